@@ -21,11 +21,17 @@ namespace qs {
 namespace {
 
 constexpr int TX = 64, TY = 4, HX = TX + 2, HY = TY + 2, HALO = HX * HY;
-constexpr int SEGZ = 32;
+// Planes per segment (at most) and workgroups wanted.  A march costs about a
+// microsecond per plane whatever the tile holds, so on small grids 32-plane
+// segments leave most CUs idle for the whole march: 29 us at 32^3 and 33 us at
+// 96^3 in FP64, against 5.4 and 18.5 us with the segments cut until there are
+// four workgroups per CU (or two planes are left).
+constexpr int kZmSeg = 32, kZmSlots = 1024;
 
 struct ZmArgs {
   int nx, ny, nz;
   int ntx, nty, nseg;
+  int seg;  // planes per segment
   int real_wgs, grid_per_xcd;
 };
 
@@ -62,7 +68,7 @@ __global__ __launch_bounds__(256) void k_residual_zm(const Tin* __restrict__ x,
   const int i = i0 + lx, j = j0 + ly;
   const bool own = (i < nx) && (j < ny);
   const size_t P = static_cast<size_t>(nx) * ny, C = static_cast<size_t>(nz + 1) * P;
-  const int z0 = 1 + sg * SEGZ, z1 = min(z0 + SEGZ, nz);
+  const int z0 = 1 + sg * a.seg, z1 = min(z0 + a.seg, nz);
 
   // halo element e of the tile -> global column offset in a plane
   size_t hoff[2];
@@ -187,7 +193,9 @@ ZmArgs zm_args(Dims d) {
   a.nz = d.nz;
   a.ntx = (d.nx + TX - 1) / TX;
   a.nty = (d.ny + TY - 1) / TY;
-  a.nseg = (d.nz - 1 + SEGZ - 1) / SEGZ;
+  a.seg = kZmSeg;
+  while (a.seg > 2 && a.ntx * a.nty * ((d.nz - 1 + a.seg - 1) / a.seg) < kZmSlots) a.seg /= 2;
+  a.nseg = (d.nz - 1 + a.seg - 1) / a.seg;
   a.real_wgs = a.ntx * a.nty * a.nseg;
   a.grid_per_xcd = (a.real_wgs + 7) / 8;
   return a;
@@ -207,11 +215,15 @@ ZmArgs zm_args(Dims d) {
 constexpr int FX = 64, FY = 8;                      // fine tile
 constexpr int RXN = FX + 1, RYN = FY + 1, RN = RXN * RYN;  // residual patch
 constexpr int XXN = FX + 3, XYN = FY + 3, XN = XXN * XYN;  // x patch
-constexpr int CSEG = 16;                            // coarse planes per segment
+// Coarse planes per segment (at most); cut for small grids as the residual's
+// are (75.7 -> 10.7 us at 32^3, 87 -> 36 us at 96^3 in FP64) until one round of
+// resident workgroups is reached: two per CU by LDS in FP64, four in FP32.
+constexpr int kRrSeg = 16;
 
 struct RrArgs {
   int nx, ny, nz;
   int ntx, nty, nseg;
+  int seg;  // coarse planes per segment
   int real_wgs, grid_per_xcd;
 };
 
@@ -232,7 +244,7 @@ __global__ __launch_bounds__(256) void k_resid_restrict(const T* __restrict__ x,
   const int nx = a.nx, ny = a.ny, nz = a.nz;
   const int nxc = nx / 2, nyc = ny / 2, nzc = nz / 2;
   const int i0 = tx * FX, j0 = ty * FY;
-  const int K0 = 1 + sg * CSEG, K1 = min(K0 + CSEG, nzc);  // coarse planes [K0, K1)
+  const int K0 = 1 + sg * a.seg, K1 = min(K0 + a.seg, nzc);  // coarse planes [K0, K1)
   const size_t P = static_cast<size_t>(nx) * ny, C = static_cast<size_t>(nz + 1) * P;
   const int tid = threadIdx.x;
 
@@ -370,14 +382,16 @@ __global__ __launch_bounds__(256) void k_resid_restrict(const T* __restrict__ x,
   }
 }
 
-RrArgs rr_args(Dims d) {
+RrArgs rr_args(Dims d, int slots) {
   RrArgs a;
   a.nx = d.nx;
   a.ny = d.ny;
   a.nz = d.nz;
   a.ntx = (d.nx + FX - 1) / FX;
   a.nty = (d.ny + FY - 1) / FY;
-  a.nseg = (d.nz / 2 - 1 + CSEG - 1) / CSEG;
+  a.seg = kRrSeg;
+  while (a.seg > 1 && a.ntx * a.nty * ((d.nz / 2 - 1 + a.seg - 1) / a.seg) < slots) a.seg /= 2;
+  a.nseg = (d.nz / 2 - 1 + a.seg - 1) / a.seg;
   a.real_wgs = a.ntx * a.nty * a.nseg;
   a.grid_per_xcd = (a.real_wgs + 7) / 8;
   return a;
@@ -423,7 +437,7 @@ void launch_resid_restrict(const T* x, const T* b, T* bc, T* xc, Dims d,
   cf.m4 = static_cast<T>(c.m4);
   cf.inv_diag = static_cast<T>(c.inv_diag);
   cf.ih2 = static_cast<T>(c.ih2);
-  const RrArgs a = rr_args(d);
+  const RrArgs a = rr_args(d, sizeof(T) == 8 ? 512 : 1024);
   hipLaunchKernelGGL((k_resid_restrict<T>), dim3(8 * a.grid_per_xcd), dim3(256), 0, s, x, b, bc, xc,
                      a, cf);
 }
