@@ -92,6 +92,13 @@ struct qs_handle {
   FineCoef<float> fc32;
   double* Ainv = nullptr;
   int ncoarse = 0;
+  // the cycle of the two coarsest levels as one map (kernels_bottom.hip), where
+  // there are three levels or more and it is supported; bottom is set once the
+  // blocks are there
+  bool bottom = false;
+  double* bottom_M = nullptr;
+  double* bottom_tw = nullptr;
+  double* bottom_yh = nullptr;
   double* partial = nullptr;
   int partial_n = 0;
   double* dnorm = nullptr;   // device, 4 doubles
@@ -104,10 +111,19 @@ struct qs_handle {
 
 namespace {
 
+// The level whose cycle (with the coarsest below it) is applied as one map, or
+// -1.  The fine level is never it: it has wall data and a start to keep.
+int bottom_level(const std::vector<int>& dims) {
+  const int l = static_cast<int>(dims.size() / 3) - 2;
+  if (l < 1) return -1;
+  return bottom_supported(Dims{dims[3 * l], dims[3 * l + 1], dims[3 * l + 2]}) ? l : -1;
+}
+
 void carve(const qs_params* p, const std::vector<int>& dims, char* base, qs_handle* hd,
            size_t* total) {
   Carver cv{base};
   const int nlev = static_cast<int>(dims.size() / 3);
+  const int bl = bottom_level(dims);
   int maxblocks = 1;
   for (int l = 0; l < nlev; ++l) {
     LevelBufs lb;
@@ -128,6 +144,12 @@ void carve(const qs_params* p, const std::vector<int>& dims, char* base, qs_hand
         lb.r32 = cv.take<float>(e);
         lb.y32 = cv.take<float>(e);
       }
+      // the setup of the bottom map runs its cycle in FP64
+      if (bl >= 1 && l >= bl) {
+        lb.x64 = cv.take<double>(e);
+        lb.b64 = cv.take<double>(e);
+        lb.r64 = cv.take<double>(e);
+      }
     }
     const size_t planes = static_cast<size_t>(lb.d.nz + 1);
     lb.S64 = cv.take<double>(planes * kStencil);
@@ -145,6 +167,17 @@ void carve(const qs_params* p, const std::vector<int>& dims, char* base, qs_hand
   double* Ainv = cv.take<double>(static_cast<size_t>(nc) * nc);
   double* partial = cv.take<double>(maxblocks);
   double* dnorm = cv.take<double>(4);
+  if (bl >= 1) {
+    const Dims d{dims[3 * bl], dims[3 * bl + 1], dims[3 * bl + 2]};
+    double* M = cv.take<double>(bottom_matrix_values(d));
+    double* yh = cv.take<double>(bottom_vector_values(d));
+    double* tw = cv.take<double>(d.nx + d.ny);
+    if (hd) {
+      hd->bottom_M = M;
+      hd->bottom_yh = yh;
+      hd->bottom_tw = tw;
+    }
+  }
   if (hd) {
     hd->nlev = nlev;
     hd->ncoarse = nc;
@@ -356,6 +389,10 @@ void vcycle(qs_handle* hd, int l, T* x, const T* b, bool x_zero = false) {
     coarse_solve<T>(hd, l, x, b, Prec<T>::r(lb));
     return;
   }
+  if (hd->bottom && l == hd->nlev - 2) {
+    launch_bottom<T>(hd->bottom_M, hd->bottom_tw, b, x, hd->bottom_yh, lb.d, hd->stream);
+    return;
+  }
   smooth<T>(hd, l, x, b, hd->p.n_pre, false, x_zero);
   LevelBufs& cb = hd->L[l + 1];
   // the restriction also clears the interior of the coarse correction (its
@@ -375,6 +412,18 @@ void vcycle(qs_handle* hd, int l, T* x, const T* b, bool x_zero = false) {
   }
   launch_prolong_add<T>(x, Prec<T>::x(cb), lb.d, hd->stream);
   smooth<T>(hd, l, x, b, hd->p.n_post, true);
+}
+
+// Blocks of the bottom map: the FP64 cycle of the two coarsest levels on every
+// unit right-hand side, each response transformed into one column per mode.
+void build_bottom(qs_handle* hd) {
+  const int l = hd->nlev - 2;
+  LevelBufs& lb = hd->L[l];
+  for (int u = 0; u < bottom_unknowns(lb.d); ++u) {
+    launch_bottom_unit(lb.b64, lb.x64, lb.d, u, hd->stream);
+    vcycle<double>(hd, l, lb.x64, lb.b64);
+    launch_bottom_column(lb.x64, lb.d, hd->bottom_tw, u, hd->bottom_M, hd->stream);
+  }
 }
 
 // ||b - K x||^2 on level 0 in FP64 (optionally writing the residual, scaled,
@@ -586,6 +635,24 @@ qs_status qs_setup(const qs_params* p, void* workspace, size_t workspace_bytes, 
     const hipError_t e = hipMemcpyAsync(hd->Ainv, H.coarse_inv.data(), H.coarse_inv.size() * 8,
                                         hipMemcpyHostToDevice, hd->stream);
     if (e != hipSuccess) st = hip_fail("hipMemcpyAsync (coarse inverse)", e);
+  }
+  std::vector<double> tw;
+  if (st == QS_OK && hd->bottom_M) {
+    const Dims d = hd->L[hd->nlev - 2].d;
+    for (const int n : {d.nx / 2, d.ny / 2})
+      for (int s = 0; s < n; ++s) {
+        const double a = 2.0 * 3.14159265358979323846 * s / n;
+        tw.push_back(std::cos(a));
+        tw.push_back(std::sin(a));
+      }
+    const hipError_t e = hipMemcpyAsync(hd->bottom_tw, tw.data(), tw.size() * 8,
+                                        hipMemcpyHostToDevice, hd->stream);
+    if (e != hipSuccess) st = hip_fail("hipMemcpyAsync (roots of unity)", e);
+    if (st == QS_OK) {
+      build_bottom(hd);
+      st = launch_check();
+      hd->bottom = st == QS_OK;
+    }
   }
   {
     const hipError_t e = hipStreamSynchronize(hd->stream);

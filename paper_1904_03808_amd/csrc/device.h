@@ -144,6 +144,22 @@ void launch_zero_interior(T* x, Dims d, hipStream_t s);
 template <typename T>
 void launch_coarse_solve(const double* Ainv, int n, const T* b, T* x, Dims d, hipStream_t s);
 
+// --- the two coarsest levels as one map (kernels_bottom.hip) ---------------
+// d: the level above the coarsest.  M: the map's blocks, bottom_matrix_values
+// doubles; yh: scratch of bottom_vector_values doubles; tw: the roots of unity
+// exp(2 pi i s / cx), then exp(2 pi i s / cy) (real and imaginary parts; cx, cy
+// the coarsest sizes).
+bool bottom_supported(Dims d);
+int bottom_unknowns(Dims d);  // per block; also the unit right-hand sides of the setup
+size_t bottom_matrix_values(Dims d);
+size_t bottom_vector_values(Dims d);
+void launch_bottom_unit(double* b, double* x, Dims d, int u, hipStream_t s);
+void launch_bottom_column(const double* x, Dims d, const double* tw, int u, double* M, hipStream_t s);
+// x = (V-cycle of level d and the coarsest, from zero) b, walls not written
+template <typename T>
+void launch_bottom(const double* M, const double* tw, const T* b, T* x, double* yh, Dims d,
+                   hipStream_t s);
+
 // --- STZ / projection kernels (kernels_stz.hip) -----------------------------
 struct StzArgs {
   double s_y, tau0, beta, delta_over_T, c0, chi_inf, dt;
