@@ -23,7 +23,7 @@
 // LDS.  Planes f-2..f+1 of the row and of its two neighbour rows sit in a ring
 // of four planes.  Each LDS row holds the nx columns plus a copy of column
 // nx-1 before column 0 and of column 0 after column nx-1, so that the x
-// neighbours of every column are at fixed offsets; with the row length a
+// neighbours of every column are at fixed offsets; with the LDS row stride a
 // compile-time constant every stencil read is one base register plus an
 // immediate offset.
 //
@@ -86,16 +86,18 @@ constexpr int kPad = 2;  // LDS row: [unused][copy of col nx-1][cols 0..nx-1][co
 // again from old values, so four halo columns keep every written column exact.
 constexpr int kHalo = 4;
 constexpr int kSplitW = 384;
+constexpr int kSplitStride = kSplitW + 2 * kHalo + 2 * kPad;
 
 // rows of one parity per workgroup: two at 256 columns, more for shorter rows
 // (at most 256 threads), one at 384, 512 and 768 (384 threads)
-int rows_per_group(int nx) { return std::max(1, std::min(64, 512 / nx)); }
 
 // Per-thread state of the sweep, passed by value so that it stays in registers.
-template <typename T, int NX>
+template <typename T, int S>
 struct Ctx {
-  T* ring;   // [4 planes][2 rows + 1][3 components][NXP]: rows j0-1 .. j0+2 rows-1
-  int nx;    // row length (NX when NX > 0)
+  // ring [4 planes][2 rows + 1][3 components][S]: rows j0-1 .. j0+2 rows-1
+  T* mine;   // column 0 of this thread's row j-1, component 0, in slot 0
+  int slot;  // elements of one plane's slot
+  int nx;    // row length
   int rows;  // rows per workgroup
   int r;     // row of this thread within the workgroup (ring rows 2r .. 2r+2)
   int c0;    // first column of this thread's pair
@@ -104,7 +106,7 @@ struct Ctx {
   size_t P, C;
   bool write;  // false for rows past the last one of this parity (last group)
   // rows of 768 FP64 values: split into two column segments (see kHalo)
-  static constexpr bool kSplit = NX == 768 && sizeof(T) == 8;
+  static constexpr bool kSplit = S == kSplitStride;
   int gc0;       // global column of this thread's pair (c0 without the split)
   bool own_col;  // the pair is one the workgroup writes (not halo)
   // prolongation variants (Z = 3, 4): the coarse correction ec, its plane
@@ -113,15 +115,13 @@ struct Ctx {
   const T* ec;
   size_t Pc, Cc;
   int nzc, I, I1, JA, JB;
-  __device__ __forceinline__ int nxp() const {
-    return (kSplit ? kSplitW + 2 * kHalo : (NX > 0 ? NX : nx)) + 2 * kPad;
-  }
+  __device__ __forceinline__ constexpr int nxp() const { return S; }
   // column 0 of LDS row q = 3 rr + component of this thread's rows
   // (rr 0, 1, 2 = j-1, j, j+1) in the plane held in ring slot (plane & 3);
   // the rows of a workgroup are consecutive, so the neighbour row between two
   // of its rows is stored once
   __device__ __forceinline__ T* row(int plane, int q) const {
-    return ring + (((plane & 3) * (2 * rows + 1) + 2 * r) * 3 + q) * nxp() + kPad;
+    return mine + (plane & 3) * slot + q * S;
   }
 };
 
@@ -141,12 +141,12 @@ struct PlaneRegs {
 // the own rows read as x + T e_c (its second half: the neighbour rows come
 // corrected from the first half's output).  The correction is added where the
 // registers go into the ring (correct_plane).
-template <typename T, int NX, int Z>
-__device__ __forceinline__ void fetch_plane(const Ctx<T, NX>& c, const T* __restrict__ own_src,
+template <typename T, int S, int Z>
+__device__ __forceinline__ void fetch_plane(const Ctx<T, S>& c, const T* __restrict__ own_src,
                                             const T* __restrict__ nbr_src, int p,
                                             PlaneRegs<T>& out) {
   using V = typename V2<T>::type;
-  const int nx = NX > 0 ? NX : c.nx;
+  const int nx = c.nx;
   const size_t o = static_cast<size_t>(p) * c.P + c.gc0;
   const size_t om = o + static_cast<size_t>(c.jm) * nx;
   const size_t oo = o + static_cast<size_t>(c.j) * nx;
@@ -173,13 +173,13 @@ struct CoarseRegs {
   T e[2][2][2][3];  // [plane Ka, Ka+1][row A, B][column I, I+1][component]
 };
 
-template <typename T, int NX, int Z>
-__device__ __forceinline__ void fetch_coarse(const Ctx<T, NX>& c, int Ka, CoarseRegs<T>& out) {
+template <typename T, int S, int Z>
+__device__ __forceinline__ void fetch_coarse(const Ctx<T, S>& c, int Ka, CoarseRegs<T>& out) {
   if (Z != 3 && Z != 4) return;
 #pragma unroll
   for (int kp = 0; kp < 2; ++kp) {
     const size_t base = static_cast<size_t>(min(Ka + kp, c.nzc)) * c.Pc;
-    const int nxc = NX > 0 ? NX / 2 : c.nx / 2;
+    const int nxc = c.nx / 2;
 #pragma unroll
     for (int rb = 0; rb < (Z == 3 ? 2 : 1); ++rb) {
       const size_t o = base + static_cast<size_t>(rb ? c.JB : c.JA) * nxc;
@@ -195,8 +195,8 @@ __device__ __forceinline__ void fetch_coarse(const Ctx<T, NX>& c, int Ka, Coarse
 // x + T e_c for the fine plane p (coarse planes Ka, Ka+1 in ce) on the rows
 // of `in` that need it, in the arithmetic of k_prolong_add: the x, y
 // combination of each coarse plane, then the z mean on odd planes.
-template <typename T, int NX, int Z>
-__device__ __forceinline__ void correct_plane(const Ctx<T, NX>& c, int p, int Ka,
+template <typename T, int S, int Z>
+__device__ __forceinline__ void correct_plane(const Ctx<T, S>& c, int p, int Ka,
                                               const CoarseRegs<T>& ce, PlaneRegs<T>& in) {
   if (Z != 3 && Z != 4) return;
   const T h = T(0.5);
@@ -243,15 +243,15 @@ __device__ __forceinline__ void correct_plane(const Ctx<T, NX>& c, int p, int Ka
   }
 }
 
-template <typename T, int NX>
-__device__ __forceinline__ void store_plane(const Ctx<T, NX>& c, int p, const PlaneRegs<T>& in) {
+template <typename T, int S>
+__device__ __forceinline__ void store_plane(const Ctx<T, S>& c, int p, const PlaneRegs<T>& in) {
   using V = typename V2<T>::type;
-  const int nx = NX > 0 ? NX : c.nx;
+  const int nx = c.nx;
   // the pair holding column 0 also writes its copy after the row end, the
   // pair holding column nx-1 its copy before column 0; every other thread
   // writes its first value once more onto itself (no branch)
-  const bool hi = !Ctx<T, NX>::kSplit && c.c0 == nx - 2;
-  const int g = Ctx<T, NX>::kSplit ? c.c0 : (c.c0 == 0 ? nx : (hi ? -1 : c.c0));
+  const bool hi = !Ctx<T, S>::kSplit && c.c0 == nx - 2;
+  const int g = Ctx<T, S>::kSplit ? c.c0 : (c.c0 == 0 ? nx : (hi ? -1 : c.c0));
   T* base = c.row(p, 0);
   const int nq = c.r == c.rows - 1 ? 9 : 6;
 #pragma unroll
@@ -265,12 +265,12 @@ __device__ __forceinline__ void store_plane(const Ctx<T, NX>& c, int p, const Pl
 }
 
 // b at plane p, the plane clamped into the interior (b is used only there).
-template <typename T, int NX>
-__device__ __forceinline__ void fetch_b(const Ctx<T, NX>& c, const T* __restrict__ b, int p, int nz,
+template <typename T, int S>
+__device__ __forceinline__ void fetch_b(const Ctx<T, S>& c, const T* __restrict__ b, int p, int nz,
                                         typename V2<T>::type out[3]) {
   using V = typename V2<T>::type;
   p = min(max(p, 1), nz - 1);
-  const int nx = NX > 0 ? NX : c.nx;
+  const int nx = c.nx;
   const size_t o = static_cast<size_t>(p) * c.P + static_cast<size_t>(c.j) * nx + c.gc0;
 #pragma unroll
   for (int k = 0; k < 3; ++k) out[k] = NT2<T>::template load<V>(b + k * c.C + o);
@@ -278,8 +278,8 @@ __device__ __forceinline__ void fetch_b(const Ctx<T, NX>& c, const T* __restrict
 
 // Gauss-Seidel value of the node (row j, plane p, column col):
 // x = D^-1 (b - sum_{q != p} A_pq x_q) with the fine-operator stencil.
-template <typename T, int NX>
-__device__ __forceinline__ void gs_node(const Ctx<T, NX>& c, int p, int col, T b0, T b1, T b2,
+template <typename T, int S>
+__device__ __forceinline__ void gs_node(const Ctx<T, S>& c, int p, int col, T b0, T b1, T b2,
                                         const FineCoef<T>& cf, T& o0, T& o1, T& o2) {
   const int W = c.nxp();
   // base pointers at column col-1 of row 0 (j-1) of planes p-1, p, p+1
@@ -311,20 +311,20 @@ __device__ __forceinline__ void gs_node(const Ctx<T, NX>& c, int p, int col, T b
 
 // Update column c0 + xp of plane p and write it into the ring (and its copy
 // past the row end when it is column 0 or nx-1).
-template <typename T, int NX, int XP>
-__device__ __forceinline__ void update_phase(const Ctx<T, NX>& c, int p,
+template <typename T, int S, int XP>
+__device__ __forceinline__ void update_phase(const Ctx<T, S>& c, int p,
                                              const typename V2<T>::type bv[3],
                                              const FineCoef<T>& cf, T o[3]) {
-  const int nx = NX > 0 ? NX : c.nx;
+  const int nx = c.nx;
   const int col = c.c0 + XP;
   const T b0 = XP ? bv[0].y : bv[0].x;
   const T b1 = XP ? bv[1].y : bv[1].x;
   const T b2 = XP ? bv[2].y : bv[2].x;
-  gs_node<T, NX>(c, p, col, b0, b1, b2, cf, o[0], o[1], o[2]);
+  gs_node<T, S>(c, p, col, b0, b1, b2, cf, o[0], o[1], o[2]);
   T* own = c.row(p, 3);
   const int W = c.nxp();
   // copy of column 0 after the row end / of column nx-1 before column 0
-  const int g = Ctx<T, NX>::kSplit ? col : (col == 0 ? nx : (col == nx - 1 ? -1 : col));
+  const int g = Ctx<T, S>::kSplit ? col : (col == 0 ? nx : (col == nx - 1 ? -1 : col));
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
     own[k * W + col] = o[k];
@@ -334,17 +334,17 @@ __device__ __forceinline__ void update_phase(const Ctx<T, NX>& c, int p,
 
 // Both x-parity phases of plane p (barrier between them); the updated pair is
 // written to dst if p lies in this workgroup's segment [z0, z1).
-template <typename T, int NX, int X1>
-__device__ __forceinline__ void update_plane(const Ctx<T, NX>& c, int p, int z0, int z1,
+template <typename T, int S, int X1>
+__device__ __forceinline__ void update_plane(const Ctx<T, S>& c, int p, int z0, int z1,
                                              const typename V2<T>::type bv[3],
                                              const FineCoef<T>& cf, T* __restrict__ dst) {
   using V = typename V2<T>::type;
   T oa[3], ob[3];
-  update_phase<T, NX, X1>(c, p, bv, cf, oa);
+  update_phase<T, S, X1>(c, p, bv, cf, oa);
   __syncthreads();
-  update_phase<T, NX, 1 - X1>(c, p, bv, cf, ob);
+  update_phase<T, S, 1 - X1>(c, p, bv, cf, ob);
   if (c.write && c.own_col && p >= z0 && p < z1) {
-    const int nx = NX > 0 ? NX : c.nx;
+    const int nx = c.nx;
     const size_t o = static_cast<size_t>(p) * c.P + static_cast<size_t>(c.j) * nx + c.gc0;
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
@@ -366,42 +366,42 @@ struct StepRegs {
 };
 
 // Issue the loads of the step whose planes are g = f+2 and g+1.
-template <typename T, int NX, int Z>
-__device__ __forceinline__ void fetch_step(const Ctx<T, NX>& c, const T* __restrict__ own_src,
+template <typename T, int S, int Z>
+__device__ __forceinline__ void fetch_step(const Ctx<T, S>& c, const T* __restrict__ own_src,
                                            const T* __restrict__ nbr_src, const T* __restrict__ b,
                                            int g, int nz, StepRegs<T, Z>& s) {
-  fetch_b<T, NX>(c, b, g, nz, s.bf);
-  fetch_b<T, NX>(c, b, g - 1, nz, s.bs);
-  fetch_plane<T, NX, Z>(c, own_src, nbr_src, min(g, nz), s.p2);
-  fetch_plane<T, NX, Z>(c, own_src, nbr_src, min(g + 1, nz), s.p3);
-  fetch_coarse<T, NX, Z>(c, min(g, nz) >> 1, s.ce[0]);
+  fetch_b<T, S>(c, b, g, nz, s.bf);
+  fetch_b<T, S>(c, b, g - 1, nz, s.bs);
+  fetch_plane<T, S, Z>(c, own_src, nbr_src, min(g, nz), s.p2);
+  fetch_plane<T, S, Z>(c, own_src, nbr_src, min(g + 1, nz), s.p3);
+  fetch_coarse<T, S, Z>(c, min(g, nz) >> 1, s.ce[0]);
 }
 
 // One step of the march: issue the loads for two steps ahead into `nxt`,
 // update planes f and f-1 from the ring, then move `cur` (planes f+2, f+3)
 // into the slots of f-2 and f-1 and its b values into bf / bs.
-template <typename T, int NX, int X1, int Z>
-__device__ __forceinline__ void march_step(const Ctx<T, NX>& c, const T* __restrict__ own_src,
+template <typename T, int S, int X1, int Z>
+__device__ __forceinline__ void march_step(const Ctx<T, S>& c, const T* __restrict__ own_src,
                                            const T* __restrict__ nbr_src, const T* __restrict__ b,
                                            T* __restrict__ dst, const FineCoef<T>& cf, int f,
                                            int z0, int z1, int nz, typename V2<T>::type bf[3],
                                            typename V2<T>::type bs[3], StepRegs<T, Z>& cur,
                                            StepRegs<T, Z>& nxt) {
-  fetch_step<T, NX, Z>(c, own_src, nbr_src, b, f + 4, nz, nxt);
-  update_plane<T, NX, X1>(c, f, z0, z1, bf, cf, dst);
+  fetch_step<T, S, Z>(c, own_src, nbr_src, b, f + 4, nz, nxt);
+  update_plane<T, S, X1>(c, f, z0, z1, bf, cf, dst);
   __syncthreads();
   const int sp = f - 1;  // second-parity plane below f
   if (sp >= z0 && sp <= z1 - 1 && sp >= 1) {
-    update_plane<T, NX, X1>(c, sp, z0, z1, bs, cf, dst);
+    update_plane<T, S, X1>(c, sp, z0, z1, bs, cf, dst);
     __syncthreads();
   }
   {
     const int Ka = min(f + 2, nz) >> 1;  // as fetch_step
-    correct_plane<T, NX, Z>(c, min(f + 2, nz), Ka, cur.ce[0], cur.p2);
-    correct_plane<T, NX, Z>(c, min(f + 3, nz), Ka, cur.ce[0], cur.p3);
+    correct_plane<T, S, Z>(c, min(f + 2, nz), Ka, cur.ce[0], cur.p2);
+    correct_plane<T, S, Z>(c, min(f + 3, nz), Ka, cur.ce[0], cur.p3);
   }
-  if (f + 2 <= nz) store_plane<T, NX>(c, f + 2, cur.p2);
-  if (f + 3 <= nz) store_plane<T, NX>(c, f + 3, cur.p3);
+  if (f + 2 <= nz) store_plane<T, S>(c, f + 2, cur.p2);
+  if (f + 3 <= nz) store_plane<T, S>(c, f + 3, cur.p3);
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
     bf[k] = cur.bf[k];
@@ -413,10 +413,10 @@ __device__ __forceinline__ void march_step(const Ctx<T, NX>& c, const T* __restr
 // threads per workgroup: rows * nx/2, at most 256 except for 768-column rows
 // (FP64 rows of 768 are split over two workgroups of 196 threads)
 template <typename T>
-constexpr int sweep_max_threads(int nx) { return nx == 768 && sizeof(T) == 4 ? 384 : 256; }
+constexpr int sweep_max_threads(int stride) { return stride == 768 + 2 * kPad ? 384 : 256; }
 
-template <typename T, int NX, int X1, int Z>
-__global__ __launch_bounds__(sweep_max_threads<T>(NX)) void k_sweep_rows(const T* __restrict__ own_src,
+template <typename T, int S, int X1, int Z>
+__global__ __launch_bounds__(sweep_max_threads<T>(S)) void k_sweep_rows(const T* __restrict__ own_src,
                                                     const T* __restrict__ nbr_src,
                                                     T* __restrict__ dst, const T* __restrict__ b,
                                                     const T* __restrict__ ec,
@@ -436,14 +436,15 @@ __global__ __launch_bounds__(sweep_max_threads<T>(NX)) void k_sweep_rows(const T
     group = L / a.nseg;
     sgi = L - group * a.nseg;
   }
-  Ctx<T, NX> c;
-  c.ring = reinterpret_cast<T*>(smem);
-  c.nx = NX > 0 ? NX : a.nx;
+  Ctx<T, S> c;
+  c.nx = a.nx;
   c.rows = a.rows;
-  c.tpr = (Ctx<T, NX>::kSplit ? kSplitW + 2 * kHalo : c.nx) >> 1;
+  c.tpr = (Ctx<T, S>::kSplit ? kSplitW + 2 * kHalo : c.nx) >> 1;
   c.r = threadIdx.x / c.tpr;
   c.c0 = 2 * (threadIdx.x - c.r * c.tpr);
-  if (Ctx<T, NX>::kSplit) {
+  c.slot = (2 * a.rows + 1) * 3 * S;
+  c.mine = reinterpret_cast<T*>(smem) + 6 * c.r * S + kPad;
+  if (Ctx<T, S>::kSplit) {
     int g = xseg * kSplitW - kHalo + c.c0;
     g = g < 0 ? g + c.nx : (g >= c.nx ? g - c.nx : g);
     c.gc0 = g;
@@ -497,51 +498,51 @@ __global__ __launch_bounds__(sweep_max_threads<T>(NX)) void k_sweep_rows(const T
   // walls are never used.
   const int first = f0 - 1 >= z0 ? f0 - 2 : f0 - 1;  // bottom segment: the wall plane too
   V bf[3], bs[3];
-  fetch_b<T, NX>(c, b, f0, nz, bf);
-  fetch_b<T, NX>(c, b, f0 - 1, nz, bs);
+  fetch_b<T, S>(c, b, f0, nz, bf);
+  fetch_b<T, S>(c, b, f0 - 1, nz, bs);
   StepRegs<T, Z> ra, rb;
   {
     PlaneRegs<T> q0, q1, q2, q3;
-    fetch_plane<T, NX, Z>(c, own_src, nbr_src, max(f0 - 2, 0), q0);
-    fetch_plane<T, NX, Z>(c, own_src, nbr_src, f0 - 1, q1);
-    fetch_plane<T, NX, Z>(c, own_src, nbr_src, f0, q2);
-    fetch_plane<T, NX, Z>(c, own_src, nbr_src, f0 + 1, q3);  // f0 + 1 <= nz
+    fetch_plane<T, S, Z>(c, own_src, nbr_src, max(f0 - 2, 0), q0);
+    fetch_plane<T, S, Z>(c, own_src, nbr_src, f0 - 1, q1);
+    fetch_plane<T, S, Z>(c, own_src, nbr_src, f0, q2);
+    fetch_plane<T, S, Z>(c, own_src, nbr_src, f0 + 1, q3);  // f0 + 1 <= nz
     if (Z == 3 || Z == 4) {
       // coarse planes of the fine planes f0-2 .. f0+1 (first loads of the march)
       CoarseRegs<T> lo, hi;
       const int Klo = max(f0 - 2, 0) >> 1, Khi = f0 >> 1;
-      fetch_coarse<T, NX, Z>(c, Klo, lo);
-      fetch_coarse<T, NX, Z>(c, Khi, hi);
-      correct_plane<T, NX, Z>(c, max(f0 - 2, 0), Klo, lo, q0);
+      fetch_coarse<T, S, Z>(c, Klo, lo);
+      fetch_coarse<T, S, Z>(c, Khi, hi);
+      correct_plane<T, S, Z>(c, max(f0 - 2, 0), Klo, lo, q0);
       // plane f0 - 1 needs coarse planes (f0-1)>>1 and f0>>1: within [Klo, Klo + 1]
-      correct_plane<T, NX, Z>(c, f0 - 1, Klo, lo, q1);
-      correct_plane<T, NX, Z>(c, f0, Khi, hi, q2);
-      correct_plane<T, NX, Z>(c, f0 + 1, Khi, hi, q3);
+      correct_plane<T, S, Z>(c, f0 - 1, Klo, lo, q1);
+      correct_plane<T, S, Z>(c, f0, Khi, hi, q2);
+      correct_plane<T, S, Z>(c, f0 + 1, Khi, hi, q3);
     }
-    fetch_step<T, NX, Z>(c, own_src, nbr_src, b, f0 + 2, nz, ra);
-    if (first == f0 - 2) store_plane<T, NX>(c, f0 - 2, q0);
-    store_plane<T, NX>(c, f0 - 1, q1);
-    store_plane<T, NX>(c, f0, q2);
-    store_plane<T, NX>(c, f0 + 1, q3);
+    fetch_step<T, S, Z>(c, own_src, nbr_src, b, f0 + 2, nz, ra);
+    if (first == f0 - 2) store_plane<T, S>(c, f0 - 2, q0);
+    store_plane<T, S>(c, f0 - 1, q1);
+    store_plane<T, S>(c, f0, q2);
+    store_plane<T, S>(c, f0 + 1, q3);
   }
   __syncthreads();
   for (int f = f0;; f += 4) {
-    march_step<T, NX, X1, Z>(c, own_src, nbr_src, b, dst, cf, f, z0, z1, nz, bf, bs, ra, rb);
+    march_step<T, S, X1, Z>(c, own_src, nbr_src, b, dst, cf, f, z0, z1, nz, bf, bs, ra, rb);
     if (f + 2 > flast) break;
-    march_step<T, NX, X1, Z>(c, own_src, nbr_src, b, dst, cf, f + 2, z0, z1, nz, bf, bs, rb, ra);
+    march_step<T, S, X1, Z>(c, own_src, nbr_src, b, dst, cf, f + 2, z0, z1, nz, bf, bs, rb, ra);
     if (f + 4 > flast) break;
   }
   const int sp = flast + 1;  // only when flast + 2 is the top wall (already in the ring)
-  if (sp >= z0 && sp <= z1 - 1 && sp <= nz - 1) update_plane<T, NX, X1>(c, sp, z0, z1, bs, cf, dst);
+  if (sp >= z0 && sp <= z1 - 1 && sp <= nz - 1) update_plane<T, S, X1>(c, sp, z0, z1, bs, cf, dst);
 }
 
-template <typename T, int NX>
-void launch_nx(const T* own_src, const T* nbr_src, T* dst, const T* b, const T* ec,
+template <typename T, int S>
+void launch_stride(const T* own_src, const T* nbr_src, T* dst, const T* b, const T* ec,
                const SweepArgs& a, const FineCoef<T>& cf, int zero, int threads, size_t lds,
                hipStream_t s) {
   const dim3 grid(8 * a.grid_per_xcd), block(threads);
 #define QS_SWEEP(X1, Z)                                                                        \
-  hipLaunchKernelGGL((k_sweep_rows<T, NX, X1, Z>), grid, block, lds, s, own_src, nbr_src, dst, b, \
+  hipLaunchKernelGGL((k_sweep_rows<T, S, X1, Z>), grid, block, lds, s, own_src, nbr_src, dst, b, \
                      ec, a, cf)
   if (a.x_first && zero == 3)
     QS_SWEEP(1, 3);
@@ -558,31 +559,38 @@ void launch_nx(const T* own_src, const T* nbr_src, T* dst, const T* b, const T* 
 #undef QS_SWEEP
 }
 
-template <typename T, int NX>
+// LDS row strides the kernel is built for: a row of up to stride - 4 columns
+// (the nearest one costs at most a quarter more LDS from 32 columns on).  With
+// the stride a constant every stencil read is a base register and an immediate
+// offset; with the row length a run-time value, as it was for all but five of
+// them, the address arithmetic cost more than the stencil: per FP32 sweep 581
+// -> 207 us at 320 x 320 x 160 and 161 -> 90 us at 192^3, FP64 718 -> 696 and
+// 203 -> 186 us (there the LDS leaves one workgroup per CU).
+#define QS_STRIDES(X)                                                                     \
+  X(36) X(52) X(68) X(84) X(100) X(132) X(164) X(196) X(260) X(324) X(388) X(516) X(772)
+
+int row_stride(int nx, int bytes_per_value) {
+  if (nx == 768 && bytes_per_value == 8) return kSplitStride;
+#define QS_FIT(N) \
+  if (nx + 2 * kPad <= N) return N;
+  QS_STRIDES(QS_FIT)
+#undef QS_FIT
+  return 0;
+}
+
+template <typename T, int S>
 void set_lds_limit_one(int bytes) {
-  const void* k[6] = {reinterpret_cast<const void*>(&k_sweep_rows<T, NX, 0, 0>),
-                      reinterpret_cast<const void*>(&k_sweep_rows<T, NX, 1, 0>),
-                      reinterpret_cast<const void*>(&k_sweep_rows<T, NX, 0, 1>),
-                      reinterpret_cast<const void*>(&k_sweep_rows<T, NX, 0, 2>),
-                      reinterpret_cast<const void*>(&k_sweep_rows<T, NX, 1, 3>),
-                      reinterpret_cast<const void*>(&k_sweep_rows<T, NX, 1, 4>)};
+  const void* k[6] = {reinterpret_cast<const void*>(&k_sweep_rows<T, S, 0, 0>),
+                      reinterpret_cast<const void*>(&k_sweep_rows<T, S, 1, 0>),
+                      reinterpret_cast<const void*>(&k_sweep_rows<T, S, 0, 1>),
+                      reinterpret_cast<const void*>(&k_sweep_rows<T, S, 0, 2>),
+                      reinterpret_cast<const void*>(&k_sweep_rows<T, S, 1, 3>),
+                      reinterpret_cast<const void*>(&k_sweep_rows<T, S, 1, 4>)};
   for (const void* f : k)
     (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
 }
 
-template <typename T>
-void set_lds_limit_all(int bytes) {
-  set_lds_limit_one<T, 0>(bytes);
-  set_lds_limit_one<T, 128>(bytes);
-  set_lds_limit_one<T, 256>(bytes);
-  set_lds_limit_one<T, 384>(bytes);
-  set_lds_limit_one<T, 512>(bytes);
-  set_lds_limit_one<T, 768>(bytes);
-}
-
 }  // namespace
-
-int sweep_rows_per_group(int nx) { return rows_per_group(nx); }
 
 // column segments per row and threads per row of the row sweep
 int column_segments(int nx, int bytes_per_value) { return nx == 768 && bytes_per_value == 8 ? 2 : 1; }
@@ -590,19 +598,34 @@ int threads_per_row(int nx, int bytes_per_value) {
   return column_segments(nx, bytes_per_value) == 2 ? (kSplitW + 2 * kHalo) / 2 : nx / 2;
 }
 
+// LDS of R rows of one parity per workgroup
+int ring_bytes(int R, int nx, int bytes_per_value) {
+  return 4 * (2 * R + 1) * 3 * row_stride(nx, bytes_per_value) * bytes_per_value;
+}
+
+// Rows of one parity per workgroup: two at 256 columns, more for shorter rows
+// (at most 256 threads and 128 KB of LDS), one at 384, 512 and 768 (384
+// threads).
+int rows_per_group(int nx, int bytes_per_value) {
+  int R = std::max(1, std::min(64, 512 / nx));
+  while (R > 1 && ring_bytes(R, nx, bytes_per_value) > 128 * 1024) --R;
+  return R;
+}
+
 template <typename T>
 int blocks_per_cu(Dims d, int threads, size_t lds) {
   int n = 0;
   const void* k = nullptr;
-  switch (d.nx) {
-    case 128: k = reinterpret_cast<const void*>(&k_sweep_rows<T, 128, 0, 0>); break;
-    case 256: k = reinterpret_cast<const void*>(&k_sweep_rows<T, 256, 0, 0>); break;
-    case 384: k = reinterpret_cast<const void*>(&k_sweep_rows<T, 384, 0, 0>); break;
-    case 512: k = reinterpret_cast<const void*>(&k_sweep_rows<T, 512, 0, 0>); break;
-    case 768: k = reinterpret_cast<const void*>(&k_sweep_rows<T, 768, 0, 0>); break;
-    default: k = reinterpret_cast<const void*>(&k_sweep_rows<T, 0, 0, 0>); break;
+  switch (row_stride(d.nx, sizeof(T))) {
+#define QS_KERNEL(N) \
+  case N: k = reinterpret_cast<const void*>(&k_sweep_rows<T, N, 0, 0>); break;
+    QS_STRIDES(QS_KERNEL)
+#undef QS_KERNEL
+    default:
+      if constexpr (sizeof(T) == 8)
+        k = reinterpret_cast<const void*>(&k_sweep_rows<T, kSplitStride, 0, 0>);
   }
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k, threads, lds) != hipSuccess) n = 1;
+  if (!k || hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k, threads, lds) != hipSuccess) n = 1;
   return std::max(n, 1);
 }
 
@@ -614,7 +637,7 @@ int sweep_segment_length(Dims d, int bytes_per_value) {
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
     cus = 256;
-  const int R = rows_per_group(d.nx);
+  const int R = rows_per_group(d.nx, bytes_per_value);
   const int threads = R * threads_per_row(d.nx, bytes_per_value);
   const size_t lds = static_cast<size_t>(sweep_lds_bytes(d, bytes_per_value));
   const int per_cu = bytes_per_value == 8 ? blocks_per_cu<double>(d, threads, lds)
@@ -635,8 +658,7 @@ int sweep_segment_length(Dims d, int bytes_per_value) {
 }
 
 int sweep_lds_bytes(Dims d, int bytes_per_value) {
-  const int w = column_segments(d.nx, bytes_per_value) == 2 ? kSplitW + 2 * kHalo : d.nx;
-  return 4 * (2 * rows_per_group(d.nx) + 1) * 3 * (w + 2 * kPad) * bytes_per_value;
+  return ring_bytes(rows_per_group(d.nx, bytes_per_value), d.nx, bytes_per_value);
 }
 
 bool sweep_supported(Dims d, size_t lds_limit, int bytes_per_value) {
@@ -658,7 +680,7 @@ void launch_sweep_half(const T* own_src, const T* nbr_src, T* dst, const T* b, c
   a.x_first = x_first;
   a.seg = seg;
   a.nseg = (d.nz - 1 + seg - 1) / seg;
-  a.rows = rows_per_group(d.nx);
+  a.rows = rows_per_group(d.nx, sizeof(T));
   const int rows = (d.ny - row_par + 1) / 2;
   a.ngroups = (rows + a.rows - 1) / a.rows;
   a.xs = column_segments(d.nx, sizeof(T));
@@ -667,19 +689,28 @@ void launch_sweep_half(const T* own_src, const T* nbr_src, T* dst, const T* b, c
   a.seg_major = seg_major;
   const int threads = a.rows * threads_per_row(d.nx, sizeof(T));
   const size_t lds = static_cast<size_t>(sweep_lds_bytes(d, sizeof(T)));
-  switch (d.nx) {
-    case 128: launch_nx<T, 128>(own_src, nbr_src, dst, b, ec, a, cf, zero, threads, lds, s); break;
-    case 256: launch_nx<T, 256>(own_src, nbr_src, dst, b, ec, a, cf, zero, threads, lds, s); break;
-    case 384: launch_nx<T, 384>(own_src, nbr_src, dst, b, ec, a, cf, zero, threads, lds, s); break;
-    case 512: launch_nx<T, 512>(own_src, nbr_src, dst, b, ec, a, cf, zero, threads, lds, s); break;
-    case 768: launch_nx<T, 768>(own_src, nbr_src, dst, b, ec, a, cf, zero, threads, lds, s); break;
-    default: launch_nx<T, 0>(own_src, nbr_src, dst, b, ec, a, cf, zero, threads, lds, s); break;
+  switch (row_stride(d.nx, sizeof(T))) {
+#define QS_LAUNCH(N) \
+  case N: launch_stride<T, N>(own_src, nbr_src, dst, b, ec, a, cf, zero, threads, lds, s); break;
+    QS_STRIDES(QS_LAUNCH)
+#undef QS_LAUNCH
+    default:
+      if constexpr (sizeof(T) == 8)
+        launch_stride<T, kSplitStride>(own_src, nbr_src, dst, b, ec, a, cf, zero, threads, lds, s);
   }
 }
 
+template <typename T>
+void set_lds_limit_all(size_t bytes) {
+#define QS_LIMIT(N) set_lds_limit_one<T, N>(static_cast<int>(bytes));
+  QS_STRIDES(QS_LIMIT)
+#undef QS_LIMIT
+  if constexpr (sizeof(T) == 8) set_lds_limit_one<T, kSplitStride>(static_cast<int>(bytes));
+}
+
 void sweep_set_lds_limit(size_t bytes) {
-  set_lds_limit_all<double>(static_cast<int>(bytes));
-  set_lds_limit_all<float>(static_cast<int>(bytes));
+  set_lds_limit_all<double>(bytes);
+  set_lds_limit_all<float>(bytes);
 }
 
 template void launch_sweep_half<double>(const double*, const double*, double*, const double*,
