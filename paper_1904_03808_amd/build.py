@@ -12,7 +12,7 @@ LIB = os.path.join(PKG, "libqsmg.so")
 BUILD = os.path.join(PKG, "_build")
 
 HIP_SOURCES = ["kernels_mg.hip", "kernels_sweep.hip", "kernels_resid.hip", "kernels_stz.hip",
-               "kernels_bottom.hip", "api.hip"]
+               "kernels_bottom.hip", "kernels_tile.hip", "api.hip"]
 HOST_SOURCES = ["hierarchy.cpp"]
 # Packed FP32 instructions are disabled for all device code.
 HIP_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",

@@ -332,8 +332,8 @@ bool use_row_sweep(qs_handle* hd, int l) {
 // x_zero: the interior of x is known to be zero (its walls are zero too), so
 // the first forward sweep does not read it; the sweep writes every interior
 // node of the other buffer, so x need not even hold zeros then.
-// prolong: the coarse correction of level l + 1 (reverse sweeps on a level
-// with the row sweep only): the first sweep adds x += T prolong on the fly
+// prolong: the coarse correction of level l + 1 (reverse sweeps by the row
+// kernel only, not by tiles): the first sweep adds x += T prolong on the fly
 // instead of a separate prolongation.
 template <typename T>
 void smooth(qs_handle* hd, int l, T* x, const T* b, int sweeps, bool reverse,
@@ -364,10 +364,19 @@ void smooth(qs_handle* hd, int l, T* x, const T* b, int sweeps, bool reverse,
   T* cur = x;
   T* oth = y;
   const int rp0 = reverse ? 1 : 0, pf = reverse ? 1 : 0, xf = reverse ? 1 : 0;
+  int halves = 0;
+  const int tr = sweep_tile_rows(lb.d, hd->lds_limit, sizeof(T), &halves);
   for (int s = 0; s < sweeps; ++s) {
     const bool z = x_zero && s == 0 && !reverse;
     const bool pro = prolong && s == 0 && reverse;
     const T* ec = pro ? prolong : nullptr;
+    if (tr > 0) {
+      launch_sweep_tile<T>(cur, cur, oth, b, lb.d, tr, halves, rp0, reverse, z ? 2 : 0, cf, hd->stream);
+      if (halves == 1)
+        launch_sweep_tile<T>(cur, oth, oth, b, lb.d, tr, 1, 1 - rp0, reverse, z ? 1 : 0, cf, hd->stream);
+      std::swap(cur, oth);
+      continue;
+    }
     launch_sweep_half<T>(cur, cur, oth, b, ec, lb.d, rp0, pf, xf, cf, Prec<T>::seg(lb), 1,
                          z ? 2 : (pro ? 3 : 0), hd->stream);
     launch_sweep_half<T>(cur, oth, oth, b, ec, lb.d, 1 - rp0, pf, xf, cf, Prec<T>::seg(lb), 1,
@@ -405,7 +414,9 @@ void vcycle(qs_handle* hd, int l, T* x, const T* b, bool x_zero = false) {
     launch_restrict<T>(r, Prec<T>::b(cb), Prec<T>::x(cb), lb.d, hd->stream);
   }
   vcycle<T>(hd, l + 1, Prec<T>::x(cb), Prec<T>::b(cb));
-  if (hd->p.n_post >= 1 && use_row_sweep<T>(hd, l)) {
+  int halves = 0;
+  if (hd->p.n_post >= 1 && use_row_sweep<T>(hd, l) &&
+      !sweep_tile_rows(lb.d, hd->lds_limit, sizeof(T), &halves)) {
     // the first post-smoothing sweep applies the prolongated correction
     smooth<T>(hd, l, x, b, hd->p.n_post, true, false, Prec<T>::x(cb));
     return;
@@ -565,6 +576,7 @@ qs_status qs_setup(const qs_params* p, void* workspace, size_t workspace_bytes, 
     else
       hd->lds_limit = 65536;
     sweep_set_lds_limit(hd->lds_limit);
+    tile_set_lds_limit(hd->lds_limit);
   }
   hd->fc64.h2 = h * h;
   hd->fc64.p = lam + 2.0 * mu;

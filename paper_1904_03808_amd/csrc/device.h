@@ -82,11 +82,23 @@ template <typename T>
 void launch_sweep_half(const T* own_src, const T* nbr_src, T* dst, const T* b, const T* ec, Dims d,
                        int row_par, int plane_first, int x_first, const FineCoef<T>& cf, int seg,
                        int seg_major, int zero, hipStream_t s);
-int sweep_rows_per_group(int nx);  // rows of one parity per workgroup
 int sweep_segment_length(Dims d, int bytes_per_value);  // z planes per workgroup
 int sweep_lds_bytes(Dims d, int bytes_per_value);
 bool sweep_supported(Dims d, size_t lds_limit, int bytes_per_value);
 void sweep_set_lds_limit(size_t bytes);
+
+// Fine-level sweep by tiles held in LDS, for small grids (kernels_tile.hip).
+// halves = 2: one whole sweep, dst = src after the eight colours, rows of parity
+// row_first first, planes and columns of parity 0 first (reverse: 1); nbr is
+// src.  halves = 1: the rows of parity row_first alone, from src, with the rows
+// between them from nbr.  zero = 1 (halves = 1): the updated rows are known to
+// be 0 and not read; 2: all rows.  tr (rows a workgroup owns) and halves come
+// from sweep_tile_rows (0: the tile sweep is not used).
+int sweep_tile_rows(Dims d, size_t lds_limit, int bytes_per_value, int* halves);
+template <typename T>
+void launch_sweep_tile(const T* src, const T* nbr, T* dst, const T* b, Dims d, int tr, int halves,
+                       int row_first, bool reverse, int zero, const FineCoef<T>& cf, hipStream_t s);
+void tile_set_lds_limit(size_t bytes);
 
 // r = b - A x on interior nodes (walls of r = 0).  If `zero_interior`, x's
 // interior is treated as 0 (r = b - A_IB x_B).  If `partial` is non-null,

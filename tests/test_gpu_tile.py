@@ -1,0 +1,66 @@
+"""GPU parity of the fine-level sweep by tiles: row strides and their edges,
+planes and rows that leave a remainder, tiles that wrap onto themselves, whole
+sweeps and half sweeps, and the first sweep of a zero correction (FP32)."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from oracle.multigrid import MGOracle
+from workloads import lame
+
+pytestmark = pytest.mark.gpu
+LAM, MU = lame()
+
+# grid and min_coarse_nz (two levels at least): nz - 1 = 3, 5, 7, 9, 11, 13 and
+# 23 planes in tiles of 4; 96 x 96 x 24 takes half sweeps in FP64 (two rounds of
+# whole-sweep tiles), rows of 130 and 160 always do
+GRIDS = [((4, 4, 4), 2), ((34, 6, 10), 5), ((50, 8, 6), 3), ((66, 6, 14), 7), ((98, 4, 8), 4),
+         ((130, 6, 12), 6), ((160, 4, 4), 2), ((96, 96, 24), 3)]
+
+
+def pair(n, coarse, precision):
+    from paper_1904_03808_amd.qsmg import MGSolver
+    g = MGSolver(*n, 1.0 / n[2], LAM, MU, min_coarse_nz=coarse, precision=precision)
+    return g, MGOracle(*n, 1.0 / n[2], LAM, MU, min_coarse_nz=coarse)
+
+
+@pytest.mark.parametrize("n,coarse", GRIDS)
+@pytest.mark.parametrize("precision,bar", [("fp64", 1e-13), ("fp32-ir", 2e-6)])
+def test_sweeps(n, coarse, precision, bar):
+    """One and three sweeps from a random start with wall data against the
+    oracle on the same rounded inputs, to the bars of the row sweep (sums of
+    about 45 terms)."""
+    g, o = pair(n, coarse, precision)
+    nx, ny, nz = n
+    rng = np.random.default_rng(3)
+    x = rng.standard_normal((3, nz + 1, ny, nx))
+    b = rng.standard_normal((3, nz + 1, ny, nx)) * nz * nz
+    dt, rd = (torch.float64, np.float64) if precision == "fp64" else (torch.float32, np.float32)
+    x, b = x.astype(rd).astype(np.float64), b.astype(rd).astype(np.float64)
+    for sweeps in (1, 3):
+        xd = torch.from_numpy(x).cuda().to(dt)
+        g.smooth(0, xd, torch.from_numpy(b).cuda().to(dt), sweeps)
+        xr = x.copy()
+        for _ in range(sweeps):
+            o.levels[0].sweep(xr, b, o.order)
+        got = xd.double().cpu().numpy()
+        assert np.abs(got - xr).max() <= bar * np.abs(xr).max(), sweeps
+        assert np.array_equal(got[:, [0, -1]], x[:, [0, -1]])
+
+
+@pytest.mark.parametrize("n,coarse", [((34, 6, 10), 5), ((132, 16, 8), 2)])
+def test_zero_start(n, coarse):
+    """FP32 cycles, whose first sweep starts from a zero correction that is not
+    read: two solves in a row on one handle reach 1e-10 by the oracle's residual."""
+    g, o = pair(n, coarse, "fp32-ir")
+    nx, ny, nz = n
+    for seed in (5, 6):
+        rng = np.random.default_rng(seed)
+        x = rng.standard_normal((3, nz + 1, ny, nx))
+        b = rng.standard_normal((3, nz + 1, ny, nx)) * nz * nz
+        b[:, 0] = b[:, -1] = 0
+        xd = torch.from_numpy(x).cuda()
+        g.solve(torch.from_numpy(b).cuda(), xd, rtol=1e-10)
+        r = o.residual(xd.cpu().numpy(), b)
+        assert np.linalg.norm(r) <= 1.01e-10 * o.lifted_rhs_norm(b, x)
