@@ -25,8 +25,10 @@ namespace qs {
 
 namespace {
 
-constexpr int kRows = 32;            // rows of a block per workgroup
-constexpr int kGroups = 256 / kRows;  // column groups per workgroup
+constexpr int kThreads = 512;              // of the kernels that transform b
+constexpr int kRows = 32;                  // rows of a block per workgroup
+constexpr int kGroups = kThreads / kRows;  // column groups per workgroup
+constexpr int kBatch = 8;                  // loads in flight per thread in the transform
 
 // Modes (mx, my) kept: one of each conjugate pair.  mx = 0 and 2 mx = cx pair
 // (mx, my) with (mx, -my), the other mx with cx - mx.
@@ -74,12 +76,18 @@ __device__ __forceinline__ void forward_mode(const T* __restrict__ f, int nx, in
     const T* p = f + c * C + static_cast<size_t>(k) * P + ey * nx + i;
     double2 s = make_double2(0.0, 0.0);
     int ph = 0;  // (my sy) mod cy
-    for (int sy = 0; sy < cy; ++sy) {
-      const double v = static_cast<double>(p[2 * sy * nx]);
-      s.x += v * twy[ph].x;
-      s.y -= v * twy[ph].y;
-      ph += my;
-      if (ph >= cy) ph -= cy;
+    for (int s0 = 0; s0 < cy; s0 += kBatch) {
+      T v[kBatch];
+#pragma unroll
+      for (int q = 0; q < kBatch; ++q) v[q] = p[2 * min(s0 + q, cy - 1) * nx];
+#pragma unroll
+      for (int q = 0; q < kBatch; ++q)
+        if (s0 + q < cy) {
+          s.x += static_cast<double>(v[q]) * twy[ph].x;
+          s.y -= static_cast<double>(v[q]) * twy[ph].y;
+          ph += my;
+          if (ph >= cy) ph -= cy;
+        }
     }
     part[t] = s;
   }
@@ -109,10 +117,12 @@ __device__ __forceinline__ void load_twiddles(const double2* __restrict__ tw, in
 
 // One row slice of one mode's block applied to the transform of b, which every
 // slice forms itself (b is a few hundred KB and comes from L2): yh[mode][row].
-// A workgroup of 256 threads takes 32 rows and splits the columns over eight
-// groups; 32 consecutive rows of a column are one 512-byte access.
+// A workgroup of 512 threads takes 32 rows and splits the columns over sixteen
+// groups; 32 consecutive rows of a column are one 512-byte access.  The
+// transform's loads go out eight at a time (10.5 us at 8^3 under 16^3 in FP64
+// with one load after the other and 256 threads).
 template <typename T>
-__global__ __launch_bounds__(256) void k_bottom_modes(const double2* __restrict__ M,
+__global__ __launch_bounds__(kThreads) void k_bottom_modes(const double2* __restrict__ M,
                                                       const T* __restrict__ b, int nx, int ny, int nz,
                                                       const double2* __restrict__ tw,
                                                       double2* __restrict__ yh) {
@@ -120,7 +130,7 @@ __global__ __launch_bounds__(256) void k_bottom_modes(const double2* __restrict_
   const int cx = nx / 2, cy = ny / 2, n = 12 * (nz - 1);
   double2* ltw = reinterpret_cast<double2*>(smem);
   double2* bh = ltw + cx + cy;
-  double2* part = bh + n;  // 6 (nz-1) nx values, later the 256 partial sums
+  double2* part = bh + n;  // 6 (nz-1) nx values, later the partial sums
   int mx, my;
   mode_of(blockIdx.x, cx, cy, &mx, &my);
   load_twiddles(tw, cx, cy, ltw);
@@ -209,7 +219,7 @@ __global__ __launch_bounds__(256) void k_bottom_unit(double* __restrict__ b, dou
 }
 
 // Column u of every mode's block from the response x to unit u.
-__global__ __launch_bounds__(256) void k_bottom_column(const double* __restrict__ x, int nx, int ny,
+__global__ __launch_bounds__(kThreads) void k_bottom_column(const double* __restrict__ x, int nx, int ny,
                                                        int nz, const double2* __restrict__ tw, int u,
                                                        double2* __restrict__ M) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -227,7 +237,7 @@ __global__ __launch_bounds__(256) void k_bottom_column(const double* __restrict_
 
 size_t modes_lds(Dims d) {
   const size_t part = 6ull * (d.nz - 1) * d.nx;
-  return (d.nx / 2 + d.ny / 2 + 12ull * (d.nz - 1) + (part > 256 ? part : 256)) * sizeof(double2);
+  return (d.nx / 2 + d.ny / 2 + 12ull * (d.nz - 1) + (part > kThreads ? part : kThreads)) * sizeof(double2);
 }
 
 size_t back_lds(Dims d) {
@@ -266,7 +276,7 @@ void launch_bottom_unit(double* b, double* x, Dims d, int u, hipStream_t s) {
 }
 
 void launch_bottom_column(const double* x, Dims d, const double* tw, int u, double* M, hipStream_t s) {
-  hipLaunchKernelGGL(k_bottom_column, dim3(mode_count(d.nx / 2, d.ny / 2)), dim3(256), modes_lds(d), s,
+  hipLaunchKernelGGL(k_bottom_column, dim3(mode_count(d.nx / 2, d.ny / 2)), dim3(kThreads), modes_lds(d), s,
                      x, d.nx, d.ny, d.nz, reinterpret_cast<const double2*>(tw), u,
                      reinterpret_cast<double2*>(M));
 }
@@ -276,7 +286,7 @@ void launch_bottom(const double* M, const double* tw, const T* b, T* x, double* 
                    hipStream_t s) {
   const int n = bottom_unknowns(d);
   hipLaunchKernelGGL(k_bottom_modes<T>, dim3(mode_count(d.nx / 2, d.ny / 2), (n + kRows - 1) / kRows),
-                     dim3(256), modes_lds(d), s, reinterpret_cast<const double2*>(M), b, d.nx, d.ny,
+                     dim3(kThreads), modes_lds(d), s, reinterpret_cast<const double2*>(M), b, d.nx, d.ny,
                      d.nz, reinterpret_cast<const double2*>(tw), reinterpret_cast<double2*>(yh));
   hipLaunchKernelGGL(k_bottom_back<T>, dim3(3 * (d.nz - 1)), dim3(256), back_lds(d), s,
                      reinterpret_cast<const double2*>(yh), x, d.nx, d.ny, d.nz,

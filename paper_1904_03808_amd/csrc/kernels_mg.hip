@@ -374,37 +374,46 @@ struct PairSite {
   }
 };
 
-// The four-wide window of the rows j-1, j, j+1 of plane kk: w[y][0] = column
-// i0-1, [1] = i0, [2] = i0+1, [3] = i0+2; the node at column i0 + s uses
-// columns s .. s+2.  SHFL: the pairs of a row lie in W consecutive lanes of
-// one wavefront (W a power of two dividing 64), so the outer columns i0-1
-// and i0+2 are the neighbouring lanes' pair values (the periodic wrap is a
-// rotation within the row's lanes) and only the pairs are loaded: a third of
-// the load instructions.
-template <typename T, bool SHFL>
-__device__ __forceinline__ void pair_window(const T* __restrict__ x, const PairSite<T>& st,
-                                            unsigned kk, T w[3][4][3]) {
+// The four-wide window of three rows of one plane (offsets row[y], column pair
+// i0): w[y][0] = column i0-1, [1] = i0, [2] = i0+1, [3] = i0+2; the node at
+// column i0 + s uses columns s .. s+2.  Consecutive pairs lie in consecutive
+// lanes, so the outer columns i0-1 and i0+2 are the neighbouring lanes' pair
+// values and only the pairs need to be loaded by every lane: a third of the
+// load instructions.  SHFL = 1: a row's W pairs fill W lanes (W a power of two
+// dividing 64), and the periodic wrap is a rotation within them.  SHFL = 2: any
+// W; the lanes at the ends of a row or of the wavefront load their outer column
+// (two masked groups of loads with one to four lanes each).  SHFL = 0: every
+// lane loads its outer columns.  Two-colour launch on a 192 x 192 x 96 level in
+// FP32: 27.5 us with 0, 21.5 us with 2; FP64 values take two shuffles each, and
+// 2 loses to 0 there (48-wide rows: 5.2 against 4.7 us).
+template <typename T, int SHFL>
+__device__ __forceinline__ void window3(const T* __restrict__ x, unsigned C, const unsigned row[3], int W,
+                                        int p, unsigned i0, unsigned il, unsigned ir, T w[3][4][3]) {
   using V = typename Pair<T>::type;
+  const int lane = static_cast<int>(__lane_id());
   V v[3][3];
+  T el[3][3], er[3][3];
 #pragma unroll
-  for (int y = 0; y < 3; ++y) {
-    const unsigned row = kk * st.P + st.ys[y];
+  for (int y = 0; y < 3; ++y)
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      v[y][c] = *reinterpret_cast<const V*>(x + (c * st.C + row + st.i0));
-      if (!SHFL) {
-        w[y][0][c] = x[c * st.C + row + st.il];
-        w[y][3][c] = x[c * st.C + row + st.ir];
-      }
-    }
+    for (int c = 0; c < 3; ++c) v[y][c] = *reinterpret_cast<const V*>(x + (c * C + row[y] + i0));
+  const bool lo = SHFL == 0 || (SHFL == 2 && (p == 0 || lane == 0));
+  const bool hi = SHFL == 0 || (SHFL == 2 && (p == W - 1 || lane == 63));
+  if (lo) {
+#pragma unroll
+    for (int y = 0; y < 3; ++y)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) el[y][c] = x[c * C + row[y] + il];
   }
-  int lm = 0, lp = 0;  // lanes of the pairs p-1 and p+1 in the row
-  if (SHFL) {
-    const int lane = static_cast<int>(__lane_id());
-    const int base = lane & ~(st.W - 1);
-    lm = base + ((st.p + st.W - 1) & (st.W - 1));
-    lp = base + ((st.p + 1) & (st.W - 1));
+  if (hi) {
+#pragma unroll
+    for (int y = 0; y < 3; ++y)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) er[y][c] = x[c * C + row[y] + ir];
   }
+  const int base = lane & ~(W - 1);
+  const int lm = SHFL == 1 ? base + ((p + W - 1) & (W - 1)) : max(lane - 1, 0);
+  const int lp = SHFL == 1 ? base + ((p + 1) & (W - 1)) : min(lane + 1, 63);
 #pragma unroll
   for (int y = 0; y < 3; ++y)
 #pragma unroll
@@ -412,10 +421,21 @@ __device__ __forceinline__ void pair_window(const T* __restrict__ x, const PairS
       w[y][1][c] = v[y][c].x;
       w[y][2][c] = v[y][c].y;
       if (SHFL) {
-        w[y][0][c] = __shfl(v[y][c].y, lm);
-        w[y][3][c] = __shfl(v[y][c].x, lp);
+        const T a = __shfl(v[y][c].y, lm), b = __shfl(v[y][c].x, lp);
+        w[y][0][c] = lo ? el[y][c] : a;
+        w[y][3][c] = hi ? er[y][c] : b;
+      } else {
+        w[y][0][c] = el[y][c];
+        w[y][3][c] = er[y][c];
       }
     }
+}
+
+template <typename T, int SHFL>
+__device__ __forceinline__ void pair_window(const T* __restrict__ x, const PairSite<T>& st,
+                                            unsigned kk, T w[3][4][3]) {
+  const unsigned row[3] = {kk * st.P + st.ys[0], kk * st.P + st.ys[1], kk * st.P + st.ys[2]};
+  window3<T, SHFL>(x, st.C, row, st.W, st.p, st.i0, st.il, st.ir, w);
 }
 
 // Terms of neighbour plane OZ (0, 1, 2 for k-1, k, k+1) subtracted from the
@@ -464,21 +484,21 @@ __device__ __forceinline__ void apply_inv(const T* __restrict__ Di, const T acc[
 // The b-node's x neighbours of colour a (the own a-node na and that of the
 // pair on the side away from it, by a shuffle or from LDS xa), its last terms,
 // its new value, and the store of the pair.
-template <typename T, int XF, bool SHFL>
+template <typename T, int XF, int SHFL>
 __device__ __forceinline__ void pair_finish(T* __restrict__ x, const PairSite<T>& st,
                                             const T* __restrict__ Pk, const T (*xa)[256], int tid,
                                             const T na[3], T accb[3]) {
   using V = typename Pair<T>::type;
   const int pn = XF ? (st.p == 0 ? st.W - 1 : st.p - 1) : (st.p == st.W - 1 ? 0 : st.p + 1);
   const int tn = st.active ? st.rr * st.W + pn : tid;
-  // SHFL: the neighbour pair is the lane pn of the row's run of lanes, and
+  // SHFL = 1: the neighbour pair is the lane pn of the row's run of lanes, and
   // its new a-node comes by a shuffle (xa is not used)
-  const int ln = SHFL ? (static_cast<int>(__lane_id()) & ~(st.W - 1)) + pn : 0;
+  const int ln = SHFL == 1 ? (static_cast<int>(__lane_id()) & ~(st.W - 1)) + pn : 0;
   T side[2][3];
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
     side[XF][c] = na[c];  // XF = 0: left neighbour (i0) is own; XF = 1: right (i0+1)
-    side[1 - XF][c] = SHFL ? __shfl(na[c], ln) : xa[c][tn];
+    side[1 - XF][c] = SHFL == 1 ? __shfl(na[c], ln) : xa[c][tn];
   }
 #pragma unroll
   for (int s2 = 0; s2 < 2; ++s2) {
@@ -505,14 +525,14 @@ __device__ __forceinline__ void pair_finish(T* __restrict__ x, const PairSite<T>
 
 // One thread per column pair: the three neighbour planes in a loop that is
 // not unrolled, each visit issuing its loads together (128^3 and larger).
-// SHFL: the outer window columns and the neighbour pair's new a-node come by
-// lane shuffles, with no LDS exchange and no barrier.
+// SHFL = 1: the outer window columns and the neighbour pair's new a-node come
+// by lane shuffles, with no LDS exchange and no barrier.
 // The grid is one-dimensional, gx row blocks times the colour's planes, in
 // an XCD-aware order: workgroups are dealt round-robin to the 8 XCDs, and XCD
 // x takes the contiguous range [x per_xcd, (x+1) per_xcd) of (plane, row
 // block) pairs, so that the neighbour rows and planes a workgroup reads are
 // mostly fetched into the same L2 by the workgroups next to it.
-template <typename T, int XF, bool SHFL>
+template <typename T, int XF, int SHFL>
 __global__ __launch_bounds__(256) void k_colour_pair_gen(T* __restrict__ x, const T* __restrict__ b,
                                                          int nx, int ny, int nz, ColourRange cr,
                                                          int rows_per_block, int gx, int per_xcd,
@@ -545,7 +565,7 @@ __global__ __launch_bounds__(256) void k_colour_pair_gen(T* __restrict__ x, cons
   }
   T na[3];
   apply_inv<T>(Pk + kPackedInv, acca, na);
-  if (!SHFL) {
+  if (SHFL != 1) {
 #pragma unroll
     for (int c = 0; c < 3; ++c) xa[c][tid] = na[c];
     __syncthreads();
@@ -559,7 +579,7 @@ __global__ __launch_bounds__(256) void k_colour_pair_gen(T* __restrict__ x, cons
 // neighbour load of the pair is issued at once, across the three threads.
 // The partial sums of planes k-1 and k+1 meet the middle thread's in LDS;
 // the middle thread finishes the pair as above.
-template <typename T, int XF, bool SHFL>
+template <typename T, int XF, int SHFL>
 __global__ __launch_bounds__(384) void k_colour_pair_split(T* __restrict__ x,
                                                            const T* __restrict__ b, int nx,
                                                            int ny, int nz, ColourRange cr,
@@ -600,12 +620,12 @@ __global__ __launch_bounds__(384) void k_colour_pair_split(T* __restrict__ x,
       accb[c] = bb + part[0][1][c][tid] + accb[c] + part[1][1][c][tid];
     }
     apply_inv<T>(Pk + kPackedInv, acca, na);
-    if (!SHFL) {
+    if (SHFL != 1) {
 #pragma unroll
       for (int c = 0; c < 3; ++c) xa[c][tid] = na[c];
     }
   }
-  if (!SHFL) __syncthreads();
+  if (SHFL != 1) __syncthreads();
   if (oz == 1) pair_finish<T, XF, SHFL>(x, st, Pk, xa, tid, na, accb);
 }
 
@@ -614,7 +634,7 @@ __global__ __launch_bounds__(384) void k_colour_pair_split(T* __restrict__ x,
 // neighbour row serves both nodes, so a launch issues half the neighbour
 // loads of one thread per node; each node's terms are summed in the order of
 // k_residual_gen, so the two kernels give the same values.
-template <typename T, bool SHFL>
+template <typename T, int SHFL>
 __global__ __launch_bounds__(256) void k_residual_pair_gen(const T* __restrict__ x,
                                                            const T* __restrict__ b,
                                                            T* __restrict__ r, int nx, int ny,
@@ -645,34 +665,8 @@ __global__ __launch_bounds__(256) void k_residual_pair_gen(const T* __restrict__
   for (int oz = 0; oz < 3; ++oz) {
     const unsigned kk = k + oz - 1;
     T w[3][4][3];  // rows j-1, j, j+1; columns i0-1 .. i0+2
-    V v[3][3];
-#pragma unroll
-    for (int y = 0; y < 3; ++y) {
-      const unsigned row = kk * P + ys[y] * nx;
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        v[y][c] = *reinterpret_cast<const V*>(x + (c * C + row + i0));
-        if (!SHFL) {
-          w[y][0][c] = x[c * C + row + il];
-          w[y][3][c] = x[c * C + row + ir];
-        }
-      }
-    }
-    // SHFL: a row's W pairs fill W consecutive lanes (W a power of two
-    // dividing 64); the outer columns come from the neighbouring lanes
-    const int lane = static_cast<int>(__lane_id()), base = lane & ~(W - 1);
-    const int lm = base + ((p + W - 1) & (W - 1)), lp = base + ((p + 1) & (W - 1));
-#pragma unroll
-    for (int y = 0; y < 3; ++y)
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        w[y][1][c] = v[y][c].x;
-        w[y][2][c] = v[y][c].y;
-        if (SHFL) {
-          w[y][0][c] = __shfl(v[y][c].y, lm);
-          w[y][3][c] = __shfl(v[y][c].x, lp);
-        }
-      }
+    const unsigned row[3] = {kk * P + ys[0] * nx, kk * P + ys[1] * nx, kk * P + ys[2] * nx};
+    window3<T, SHFL>(x, C, row, W, p, i0, il, ir, w);
     // the planes differ in which entries are packed: one body per plane
     auto apply = [&](auto OZ) {
       constexpr int ozc = decltype(OZ)::value;
@@ -959,6 +953,12 @@ bool pair_rows_in_lanes(Dims d) {
   return d.nx % 2 == 0 && W >= 1 && W <= 64 && (W & (W - 1)) == 0;
 }
 
+// How the pair kernels get the outer columns of a row (window3).
+template <typename T>
+int pair_shuffle(Dims d) {
+  return pair_rows_in_lanes(d) ? 1 : (sizeof(T) == 4 ? 2 : 0);
+}
+
 bool colour_pair_supported(Dims d) { return d.nx % 2 == 0 && d.nx >= 2 && d.nx <= 512; }
 
 template <typename T>
@@ -972,34 +972,31 @@ void launch_colour_pair_gen(T* x, const T* b, Dims d, int colour, const T* Pst, 
   // at 128^3)
   const int rpb = std::max(1, std::min(cr.hy, 128 / W));
   const dim3 grid(blocks_for(cr.hy, rpb), cr.nk);
-  // outer window columns by lane shuffles where a row's pairs fill a power-of-two
-  // run of lanes of one wavefront
-  const bool shfl = pair_rows_in_lanes(d);
-#define QS_PAIR(KERNEL, XF, SH, G, B, ...)                                                   \
-  hipLaunchKernelGGL((KERNEL<T, XF, SH>), G, B, 0, s, x, b, d.nx, d.ny, d.nz, cr, rpb, __VA_ARGS__)
+  // outer window columns: see window3
+  const int sh = pair_shuffle<T>(d);
+#define QS_PAIR1(KERNEL, XF, G, B, ...)                                                             \
+  if (sh == 1)                                                                                      \
+    hipLaunchKernelGGL((KERNEL<T, XF, 1>), G, B, 0, s, x, b, d.nx, d.ny, d.nz, cr, rpb, __VA_ARGS__); \
+  else if (sh == 2)                                                                                 \
+    hipLaunchKernelGGL((KERNEL<T, XF, 2>), G, B, 0, s, x, b, d.nx, d.ny, d.nz, cr, rpb, __VA_ARGS__); \
+  else                                                                                              \
+    hipLaunchKernelGGL((KERNEL<T, XF, 0>), G, B, 0, s, x, b, d.nx, d.ny, d.nz, cr, rpb, __VA_ARGS__);
+#define QS_PAIR(KERNEL, G, B, ...)         \
+  if (cr.a) {                              \
+    QS_PAIR1(KERNEL, 1, G, B, __VA_ARGS__) \
+  } else {                                 \
+    QS_PAIR1(KERNEL, 0, G, B, __VA_ARGS__) \
+  }
   if (d.nx <= 64) {  // small levels: three threads per pair
-    const dim3 block(rpb * W, 3);
-    if (cr.a && shfl)
-      QS_PAIR(k_colour_pair_split, 1, true, grid, block, Pst);
-    else if (cr.a)
-      QS_PAIR(k_colour_pair_split, 1, false, grid, block, Pst);
-    else if (shfl)
-      QS_PAIR(k_colour_pair_split, 0, true, grid, block, Pst);
-    else
-      QS_PAIR(k_colour_pair_split, 0, false, grid, block, Pst);
+    const dim3 block((rpb * W + 63) / 64 * 64, 3);  // a wavefront has one neighbour plane
+    QS_PAIR(k_colour_pair_split, grid, block, Pst)
     return;
   }
   const int threads = (rpb * W + 63) / 64 * 64;
   const int gx = static_cast<int>(grid.x), per_xcd = (gx * cr.nk + 7) / 8;
   const dim3 g1(8 * per_xcd), b1(threads);
-  if (cr.a && shfl)
-    QS_PAIR(k_colour_pair_gen, 1, true, g1, b1, gx, per_xcd, Pst);
-  else if (cr.a)
-    QS_PAIR(k_colour_pair_gen, 1, false, g1, b1, gx, per_xcd, Pst);
-  else if (shfl)
-    QS_PAIR(k_colour_pair_gen, 0, true, g1, b1, gx, per_xcd, Pst);
-  else
-    QS_PAIR(k_colour_pair_gen, 0, false, g1, b1, gx, per_xcd, Pst);
+  QS_PAIR(k_colour_pair_gen, g1, b1, gx, per_xcd, Pst)
+#undef QS_PAIR1
 #undef QS_PAIR
 }
 
@@ -1007,12 +1004,13 @@ template <typename T>
 void launch_residual_pair_gen(const T* x, const T* b, T* r, Dims d, const T* Pst, hipStream_t s) {
   const dim3 grid(blocks_for(static_cast<long long>(d.nx / 2) * d.ny, 256), d.nz - 1);
   if (d.nz - 1 <= 0) return;
-  if (pair_rows_in_lanes(d))
-    hipLaunchKernelGGL((k_residual_pair_gen<T, true>), grid, dim3(256), 0, s, x, b, r, d.nx, d.ny,
-                       d.nz, Pst);
+  const int sh = pair_shuffle<T>(d);
+  if (sh == 1)
+    hipLaunchKernelGGL((k_residual_pair_gen<T, 1>), grid, dim3(256), 0, s, x, b, r, d.nx, d.ny, d.nz, Pst);
+  else if (sh == 2)
+    hipLaunchKernelGGL((k_residual_pair_gen<T, 2>), grid, dim3(256), 0, s, x, b, r, d.nx, d.ny, d.nz, Pst);
   else
-    hipLaunchKernelGGL((k_residual_pair_gen<T, false>), grid, dim3(256), 0, s, x, b, r, d.nx, d.ny,
-                       d.nz, Pst);
+    hipLaunchKernelGGL((k_residual_pair_gen<T, 0>), grid, dim3(256), 0, s, x, b, r, d.nx, d.ny, d.nz, Pst);
 }
 
 int residual_blocks(Dims d) {
