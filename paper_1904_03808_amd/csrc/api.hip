@@ -843,15 +843,14 @@ double* stz_dcell(qs_handle* hd) {
 StzArgs stz_args(qs_handle* hd, const qs_stz_params* sp) {
   StzArgs a;
   a.s_y = sp->s_y;
-  a.tau0 = sp->tau0;
   a.beta = sp->beta;
-  a.delta_over_T = sp->delta_over_T;
   a.c0 = sp->c0;
   a.chi_inf = sp->chi_inf;
   a.dt = sp->dt;
   a.lam = hd->p.lambda;
   a.mu = hd->p.mu;
   a.h = hd->p.h;
+  a.rate0 = std::exp(-sp->delta_over_T) / sp->tau0;
   a.l2 = sp->l_diff * sp->l_diff;
   a.n_sub = sp->n_sub <= 1 && sp->n_sub >= 0 ? 1 : sp->n_sub;
   a.advect = sp->advect;
@@ -997,14 +996,9 @@ qs_status qs_explicit_step(qs_handle* hd, const qs_stz_params* sp, double U_wall
   double* sstar = cv.take<double>(6 * cells(d));
   double* chi1 = cv.take<double>(cells(d));
   double* vnew = cv.take<double>(d.elems());
-  StzArgs a = stz_args(hd, sp);
-  a.advect = 1;  // the stress equation of the explicit method carries the advection
-  launch_stz_step(v, sigma, chi, sstar, chi1, stz_dcell(hd), d, a, hd->stream);
-  launch_explicit_velocity(v, sigma, vnew, d, hd->p.h, sp->dt, rho, kappa, hd->stream);
-  launch_set_walls(vnew, d, U_wall, hd->stream);
-  launch_stress_update(sstar, v, sigma, d, hd->p.h, sp->dt, hd->p.lambda, hd->p.mu, hd->stream);
-  QS_HIP(hipMemcpyAsync(v, vnew, d.elems() * sizeof(double), hipMemcpyDeviceToDevice, hd->stream));
-  QS_HIP(hipMemcpyAsync(chi, chi1, cells(d) * sizeof(double), hipMemcpyDeviceToDevice, hd->stream));
+  launch_explicit_step(v, sigma, chi, vnew, sstar, chi1, stz_dcell(hd), d, stz_args(hd, sp), U_wall, rho,
+                       kappa, hd->stream);
+  launch_copy_state(vnew, sstar, chi1, v, sigma, chi, d, hd->stream);
   return launch_check();
 }
 

@@ -174,8 +174,9 @@ void launch_bottom(const double* M, const double* tw, const T* b, T* x, double* 
 
 // --- STZ / projection kernels (kernels_stz.hip) -----------------------------
 struct StzArgs {
-  double s_y, tau0, beta, delta_over_T, c0, chi_inf, dt;
+  double s_y, beta, c0, chi_inf, dt;
   double lam, mu, h;
+  double rate0;  // exp(-delta_over_T) / tau0
   double l2;  // squared diffusion length of Eq. chi_evo (0: no diffusion term)
   int n_sub;  // plastic sub-steps: 1 single step, > 1 fixed count, -1 per cell, -2 backward Euler
   int advect; // 1: sigma* carries the advection -(v . grad) sigma (Eq. ENO)
@@ -188,8 +189,14 @@ void launch_rhs(const double* sstar, double* b, Dims d, double h, double dt, hip
 void launch_stress_update(const double* sstar, const double* v, double* out, Dims d, double h,
                           double dt, double lam, double mu, hipStream_t s);
 void launch_set_walls(double* v, Dims d, double U, hipStream_t s);
-void launch_explicit_velocity(const double* v, const double* sigma, double* vout, Dims d, double h,
-                              double dt, double rho, double kappa, hipStream_t s);
+// One step of the explicit method from (v, sigma, chi): the new state goes to
+// (vout, sout, chiout), walls of vout at (-U, 0, 0) and (U, 0, 0) (a.advect is
+// taken as 1); then launch_copy_state brings it back.
+void launch_explicit_step(const double* v, const double* sigma, const double* chi, double* vout,
+                          double* sout, double* chiout, double* dcell, Dims d, const StzArgs& a,
+                          double U, double rho, double kappa, hipStream_t s);
+void launch_copy_state(const double* v, const double* sigma, const double* chi, double* vout,
+                       double* sout, double* chiout, Dims d, hipStream_t s);
 void launch_copy_walls(double* v, const double* lo, const double* hi, Dims d, hipStream_t s);
 void launch_stz_step_vjp(const double* v, const double* sigma, const double* chi,
                          const double* g_sstar, const double* g_chi1, double* g_sigma,

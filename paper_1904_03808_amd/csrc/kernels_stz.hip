@@ -5,6 +5,8 @@
 // cell (i,j,k) has corners i..i+1, j..j+1 (wrapped), k..k+1.  Node vectors
 // are [3][nz+1][ny][nx].  One thread per cell or per interior node; these
 // kernels stream their inputs once and are HBM-bound.
+#include <algorithm>
+
 #include "device.h"
 
 namespace qs {
@@ -82,12 +84,21 @@ struct Plastic {
   double D, dD_ds, dD_dchi;
 };
 
+// cosh(b) and, for the derivative, sinh(b), b >= 0, from one exponential (two
+// below 20, where exp(-b) still counts; sinh by the library where the
+// difference would cancel).
+__device__ __forceinline__ double cosh_of(double b) {
+  const double e = exp(b);
+  return 0.5 * (b < 20.0 ? e + exp(-b) : e);
+}
+
 __device__ __forceinline__ Plastic plastic_rate(double sbar, double chi, const StzArgs& a) {
   Plastic p{0.0, 0.0, 0.0};
   if (sbar > a.s_y) {
-    const double A = exp(-1.0 / chi) * exp(-a.delta_over_T) / a.tau0;
+    const double A = exp(-1.0 / chi) * a.rate0;
     const double bs = a.beta * sbar;
-    const double ch = cosh(bs), sh = sinh(bs);
+    const double e = exp(bs), em = exp(-bs);
+    const double ch = 0.5 * (e + em), sh = bs > 1.0 ? 0.5 * (e - em) : sinh(bs);
     const double f = 1.0 - a.s_y / sbar;
     p.D = A * ch * f;
     p.dD_ds = A * (a.beta * sh * f + ch * a.s_y / (sbar * sbar));
@@ -127,11 +138,10 @@ __device__ __forceinline__ double eno_2h(double fm2, double fm1, double f0, doub
   return fp1 - fm1;
 }
 
-// D^pl alone (Eq. stz_dpl), for the sub-step loop.
-__device__ __forceinline__ double plastic_D(double sbar, double chi, const StzArgs& a) {
+// D^pl alone (Eq. stz_dpl) from A = exp(-1/chi) exp(-delta/T) / tau0.
+__device__ __forceinline__ double plastic_D(double sbar, double A, const StzArgs& a) {
   if (!(sbar > a.s_y)) return 0.0;
-  const double A = exp(-1.0 / chi) * exp(-a.delta_over_T) / a.tau0;
-  return A * cosh(a.beta * sbar) * (1.0 - a.s_y / sbar);
+  return A * cosh_of(a.beta * sbar) * (1.0 - a.s_y / sbar);
 }
 
 constexpr int kMaxSubsteps = 65536;
@@ -237,8 +247,9 @@ __global__ __launch_bounds__(256) void k_dpl_cells(const double* __restrict__ si
 // The cell update of the STZ step from the velocity gradient L, the stress S
 // and chi of cell t (and, with ADV, adv(n) = the advection term
 // (u . grad) sigma of Voigt component n, evaluated when that component is
-// written): writes sigma*[.][t] and chi'[t].
-template <bool DIFF, bool ADV, typename Adv>
+// written): writes sigma*[.][t] and chi'[t].  EXPL: sigma* + dt C : sym(L), the
+// new stress of the explicit method, whose L is that of step n throughout.
+template <bool DIFF, bool ADV, bool EXPL, typename Adv>
 __device__ __forceinline__ void stz_update(const double* __restrict__ sigma,
                                            const double* __restrict__ chi,
                                            double* __restrict__ sstar, double* __restrict__ chi1,
@@ -252,6 +263,14 @@ __device__ __forceinline__ void stz_update(const double* __restrict__ sigma,
   const Plastic pl = plastic_rate(sbar, x, a);
   const double trL = L[0][0] + L[1][1] + L[2][2];
   double xn;
+  auto write = [&](int n, double val) {
+    if (ADV) val = val - a.dt * adv(n);
+    if (EXPL) {
+      const int p = VA[n], q = VB[n];
+      val = val + a.dt * ((p == q ? a.lam * trL : 0.0) + 2.0 * a.mu * (0.5 * (L[p][q] + L[q][p])));
+    }
+    sstar[n * N + t] = val;
+  };
   if (a.n_sub == 1) {
     const double rho = pl.D > 0.0 ? pl.D / sbar : 0.0;
     // C : (rho S0) = lambda tr(rho S0) I + 2 mu rho S0, and tr(S0) = 0
@@ -265,9 +284,7 @@ __device__ __forceinline__ void stz_update(const double* __restrict__ sigma,
         SLt += S[p][m] * L[q][m];
       }
       const double rate = LS + SLt - trL * S[p][q] - 2.0 * a.mu * rho * S0[p][q];
-      double val = S[p][q] + a.dt * rate;
-      if (ADV) val = val - a.dt * adv(n);
-      sstar[n * N + t] = val;
+      write(n, S[p][q] + a.dt * rate);
     }
     xn = x + (a.dt / a.c0) * (2.0 * sbar * pl.D / a.s_y) * (a.chi_inf - x);
   } else if (a.n_sub == -2) {
@@ -275,11 +292,12 @@ __device__ __forceinline__ void stz_update(const double* __restrict__ sigma,
     // s - sbar + 2 mu dt D^pl(s) in [s_Y, sbar] by bisection; the deviator
     // shrinks to it, chi' = (chi + c chi_inf) / (1 + c)
     double s1 = sbar;
+    const double A = exp(-1.0 / x) * a.rate0;
     if (sbar > a.s_y) {
       double lo = a.s_y, hi = sbar;
       for (int it = 0; it < kImplicitBisections; ++it) {
         const double mid = 0.5 * (lo + hi);
-        const double g = mid - sbar + 2.0 * a.mu * a.dt * plastic_D(mid, x, a);
+        const double g = mid - sbar + 2.0 * a.mu * a.dt * plastic_D(mid, A, a);
         if (g < 0.0)
           lo = mid;
         else
@@ -288,7 +306,7 @@ __device__ __forceinline__ void stz_update(const double* __restrict__ sigma,
       s1 = hi;
     }
     const double scale = sbar > a.s_y ? s1 / (sbar > 0.0 ? sbar : 1.0) : 1.0;
-    const double D1 = plastic_D(s1, x, a);
+    const double D1 = plastic_D(s1, A, a);
     const double cg = (a.dt / a.c0) * (2.0 * s1 * D1 / a.s_y);
     xn = (x + cg * a.chi_inf) / (1.0 + cg);
 #pragma unroll
@@ -300,9 +318,7 @@ __device__ __forceinline__ void stz_update(const double* __restrict__ sigma,
         LS += L[p][m] * S[m][q];
         SLt += S[p][m] * L[q][m];
       }
-      double val = (S[p][q] - (1.0 - scale) * S0[p][q]) + a.dt * (LS + SLt - trL * S[p][q]);
-      if (ADV) val = val - a.dt * adv(n);
-      sstar[n * N + t] = val;
+      write(n, (S[p][q] - (1.0 - scale) * S0[p][q]) + a.dt * (LS + SLt - trL * S[p][q]));
     }
   } else {
     // sub-steps of the plastic terms from the state of step n
@@ -312,22 +328,30 @@ __device__ __forceinline__ void stz_update(const double* __restrict__ sigma,
       M = !(m < static_cast<double>(kMaxSubsteps)) ? kMaxSubsteps : (m < 1.0 ? 1 : static_cast<int>(m));
     }
     const double tau = a.dt / M;
-    double Sp[3][3], xp = x;
+    // A sub-step takes 2 mu tau D^pl/sbar of the deviator off, so the deviator
+    // keeps its direction (up to sign) and only its scale, sbar and chi change:
+    // the loop is a chain of one exponential and two divisions.  What bounds it is
+    // the chain of the cells with the most sub-steps: 256 x 256 x 128 with a hot
+    // defect 1230 -> 558 us, against a tensor, a square root and a cosh per step.
+    // cosh(b) exp(-1/chi) = exp(b - 1/chi) (1 + exp(-2 b)) / 2, the second term
+    // below the rounding from b = 20 on.
+    const double take = 2.0 * a.mu * tau, grow = (tau / a.c0) * 2.0 / a.s_y;
+    double xp = x, sb = sbar, drop = 0.0;  // drop: the part of the deviator taken off
+    for (int it = 0; it < M; ++it) {
+      if (!(sb > a.s_y)) break;  // at or below yield nothing changes any more
+      const double b = a.beta * sb, is = 1.0 / sb;
+      double e = 0.5 * exp(b - 1.0 / xp);
+      if (b < 20.0) e += e * exp(-2.0 * b);
+      const double D = a.rate0 * e * (1.0 - a.s_y * is);
+      drop += (1.0 - drop) * (take * (D * is));
+      xp += grow * (sb * D) * (a.chi_inf - xp);
+      sb = fabs(sb - take * D);
+    }
+    double Sp[3][3];
 #pragma unroll
     for (int p = 0; p < 3; ++p)
 #pragma unroll
-      for (int q = 0; q < 3; ++q) Sp[p][q] = S[p][q];
-    for (int it = 0; it < M; ++it) {
-      double P0[3][3], sb;
-      deviator(Sp, P0, &sb);
-      const double D = plastic_D(sb, xp, a);
-      const double r = D > 0.0 ? D / sb : 0.0;
-#pragma unroll
-      for (int p = 0; p < 3; ++p)
-#pragma unroll
-        for (int q = 0; q < 3; ++q) Sp[p][q] = Sp[p][q] - tau * (2.0 * a.mu * r * P0[p][q]);
-      xp = xp + (tau / a.c0) * (2.0 * sb * D / a.s_y) * (a.chi_inf - xp);
-    }
+      for (int q = 0; q < 3; ++q) Sp[p][q] = S[p][q] - drop * S0[p][q];
 #pragma unroll
     for (int n = 0; n < 6; ++n) {
       const int p = VA[n], q = VB[n];
@@ -337,9 +361,7 @@ __device__ __forceinline__ void stz_update(const double* __restrict__ sigma,
         LS += L[p][m] * S[m][q];
         SLt += S[p][m] * L[q][m];
       }
-      double val = Sp[p][q] + a.dt * (LS + SLt - trL * S[p][q]);
-      if (ADV) val = val - a.dt * adv(n);
-      sstar[n * N + t] = val;
+      write(n, Sp[p][q] + a.dt * (LS + SLt - trL * S[p][q]));
     }
     xn = xp;
   }
@@ -366,7 +388,7 @@ __global__ __launch_bounds__(256) void k_stz_step(const double* __restrict__ v,
   double L[3][3], S[3][3];
   cell_gradient(v, nx, ny, nz, c, 0.25 / a.h, L);
   load_voigt(sigma, nx * ny * nz, t, S);
-  stz_update<DIFF, false>(sigma, chi, sstar, chi1, Dcell, nx, ny, nz, c, t, L, S, chi[t],
+  stz_update<DIFF, false, false>(sigma, chi, sstar, chi1, Dcell, nx, ny, nz, c, t, L, S, chi[t],
                           [](int) { return 0.0; }, a);
 }
 
@@ -390,33 +412,45 @@ __device__ __forceinline__ double z_layer(const double* __restrict__ f, int P, i
 // a workgroup per 16 x 16 tile of one cell plane.  Eq. ENO reads two cells on
 // each side along x, y and z; x and y come from the tile staged in LDS, and
 // the mapping keeps the z reads in cache: a band of 16 rows (all tiles along
-// x) goes to one XCD (workgroup w runs on XCD w mod 8), whose workgroups take
-// the band plane after plane and tile after tile.  The planes k-2 .. k+2 of a
+// x), or a segment of its planes (adv_grid), goes to one XCD (workgroup w runs on
+// XCD w mod 8), whose workgroups take it plane after plane and tile after tile.  The planes k-2 .. k+2 of a
 // band are then in flight together and share that XCD's L2.  Each derivative
 // is Eq. ENO along its axis (x and y wrap; in z the layers past the walls
 // continue the two nearest layers linearly, Sec. 3.5), with u the mean of the
 // cell's eight corner velocities; no fused multiply-adds here, so the branch
 // choices of Eq. ENO are taken on the same FP64 values as the oracle's.
 constexpr int kTile = 16;
+constexpr int kW = kTile + 4;         // staged rows and columns
+constexpr int kT = kTile * kTile;     // threads
+constexpr int kStage = 6 * kW * (kW + 1);
 
-template <bool DIFF>
-__global__ __launch_bounds__(kTile * kTile) void k_stz_step_adv(const double* __restrict__ v,
-                                                               const double* __restrict__ sigma,
-                                                               const double* __restrict__ chi,
-                                                               double* __restrict__ sstar,
-                                                               double* __restrict__ chi1,
-                                                               const double* __restrict__ Dcell,
-                                                               int nx, int ny, int nz, int ntx,
-                                                               int bands, StzArgs a) {
+// One workgroup's tile.  All six components of plane k over the tile and two
+// cells around it (x and y wrap) are staged in LDS at once, with the tile's
+// corner nodes (17 x 17 columns, node planes k and k+1): one round of loads and
+// one barrier, and each value is loaded once instead of by the cells or corners
+// that use it.  The six advection terms follow one component at a time (a loop
+// that is not unrolled keeps one copy of the stencil code and few registers),
+// the four z neighbours of the cell's own column coming from memory one
+// component ahead; the terms are parked in LDS, over the corner nodes, until the
+// update writes each component.  Staging one component after the other took
+// twelve barriers, each behind a load: 281 us at 192 x 192 x 96 (one plastic
+// step, no diffusion) against 243 us, and 197 us with the segments of adv_grid.
+template <bool DIFF, bool EXPL>
+__device__ __forceinline__ void advected_tile(int w, const double* __restrict__ v,
+                                              const double* __restrict__ sigma,
+                                              const double* __restrict__ chi,
+                                              double* __restrict__ sstar, double* __restrict__ chi1,
+                                              const double* __restrict__ Dcell, int nx, int ny, int nz,
+                                              int ntx, int bands, int kz, const StzArgs& a,
+                                              double* __restrict__ tl, double* __restrict__ pool) {
 #pragma clang fp contract(off)
-  const int w = blockIdx.x;
-  const int xcd = w & 7, slot = w >> 3;
-  const int per_band = nz * ntx;
-  const int band = (slot / per_band) * 8 + xcd;
-  if (band >= bands) return;
-  const int r = slot - (slot / per_band) * per_band;
-  const int k = r / ntx, tx = r - k * ntx;
-  const int lx = static_cast<int>(threadIdx.x) % kTile, ly = static_cast<int>(threadIdx.x) / kTile;
+  const int slot = w >> 3, per = kz * ntx;
+  const int unit = (slot / per) * 8 + (w & 7);
+  const int r = slot % per, seg = unit / bands, band = unit - seg * bands;
+  const int k = seg * kz + r / ntx, tx = r % ntx;
+  if (k >= nz) return;
+  const int tid = static_cast<int>(threadIdx.x);
+  const int lx = tid % kTile, ly = tid / kTile;
   const int i0 = tx * kTile, j0 = band * kTile;
   // cells past the grid edge (ragged last tile) compute on a clamped cell and
   // write nothing; they take part in the staging and the barriers
@@ -430,99 +464,102 @@ __global__ __launch_bounds__(kTile * kTile) void k_stz_step_adv(const double* __
   const int P = nx * ny, N = P * nz;
   const int col = c.j * nx + c.i;
   const int t = k * P + col;
-  // The six advection terms, one component at a time (a loop that is not
-  // unrolled keeps one copy of the stencil code and few registers), parked in
-  // LDS slots of this thread until the update writes each component.  The
-  // component's plane k over the tile and two cells around it (x and y wrap)
-  // is staged in LDS, so each value is loaded once instead of by the five
-  // cells that use it; the four z neighbours of the cell's own column come
-  // from memory.  The next component's values are loaded while one is
-  // computed.  Before that, the tile's corner nodes (17 x 17 columns, node
-  // planes k and k+1) pass through the same LDS as advs and fcell, so each
-  // node is loaded once instead of by the eight cells around it.
-  constexpr int kW = kTile + 4;  // staged rows and columns
-  constexpr int kT = kTile * kTile;
-  __shared__ double pool[2 * 6 * kT];
-  double(*advs)[kT] = reinterpret_cast<double(*)[kT]>(pool);
-  double(*fcell)[kT] = reinterpret_cast<double(*)[kT]>(pool + 6 * kT);  // the cell's own sigma
   double(*vt)[2][kTile + 1][kTile + 2] = reinterpret_cast<double(*)[2][kTile + 1][kTile + 2]>(pool);
-  static_assert(3 * 2 * (kTile + 1) * (kTile + 2) <= 2 * 6 * kT, "corner nodes fit the pool");
-  __shared__ double tl[kW][kW + 1];
+  double(*advs)[kT] = reinterpret_cast<double(*)[kT]>(pool);
   const double ih2 = 1.0 / (2.0 * a.h);
-  int soff[2];  // plane offsets of this thread's two staged cells (the second may be unused)
-#pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    const int e = min(static_cast<int>(threadIdx.x) + q * kT, kW * kW - 1);
-    const int sy = e / kW, sx = e - sy * kW;
-    const int gj = ((j0 - 2 + sy) % ny + ny) % ny, gi = ((i0 - 2 + sx) % nx + nx) % nx;
-    soff[q] = gj * nx + gi;
-  }
-  const bool second = static_cast<int>(threadIdx.x) + kT < kW * kW;
-  auto fetch = [&](int n, double sv[2], double zv[4]) {
+  auto fetch_z = [&](int n, double zv[4]) {
     const double* g = sigma + n * N;
-    sv[0] = g[k * P + soff[0]];
-    sv[1] = g[k * P + soff[1]];
     const int ks[4] = {k - 2, k - 1, k + 1, k + 2};
 #pragma unroll
     for (int q = 0; q < 4; ++q) zv[q] = z_layer(g, P, nz, col, ks[q]);
   };
-  double sv[2], zv[4];
-  fetch(0, sv, zv);
   {
-    constexpr int kNodes = 3 * 2 * (kTile + 1) * (kTile + 1);
-    constexpr int kPer = (kNodes + kT - 1) / kT;
-    double nv[kPer];
-    int comp[kPer], dz[kPer], yy[kPer], xx[kPer];
+    double sv[6][2];
+    int at[2];
 #pragma unroll
-    for (int q = 0; q < kPer; ++q) {
-      const int e = min(static_cast<int>(threadIdx.x) + q * kT, kNodes - 1);
-      comp[q] = e / (2 * (kTile + 1) * (kTile + 1));
-      const int rem = e - comp[q] * 2 * (kTile + 1) * (kTile + 1);
-      dz[q] = rem / ((kTile + 1) * (kTile + 1));
-      const int rem2 = rem - dz[q] * (kTile + 1) * (kTile + 1);
-      yy[q] = rem2 / (kTile + 1);
-      xx[q] = rem2 - yy[q] * (kTile + 1);
-      const int gi = (i0 + xx[q]) % nx, gj = (j0 + yy[q]) % ny;
-      nv[q] = v[comp[q] * (nz + 1) * P + (k + dz[q]) * P + gj * nx + gi];
+    for (int q = 0; q < 2; ++q) {
+      const int e = min(tid + q * kT, kW * kW - 1);
+      const int sy = e / kW, sx = e - sy * kW;
+      const int gj = ((j0 - 2 + sy) % ny + ny) % ny, gi = ((i0 - 2 + sx) % nx + nx) % nx;
+      at[q] = sy * (kW + 1) + sx;
+      const double* g = sigma + k * P + gj * nx + gi;
+#pragma unroll
+      for (int n = 0; n < 6; ++n) sv[n][q] = g[n * N];
+    }
+    constexpr int kNodes = (kTile + 1) * (kTile + 1);  // of one component and plane
+    double nv[2][6];
+    int nat[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int e = min(tid + q * kT, kNodes - 1);
+      const int yy = e / (kTile + 1), xx = e - yy * (kTile + 1);
+      nat[q] = yy * (kTile + 2) + xx;
+      const double* g = v + k * P + ((j0 + yy) % ny) * nx + (i0 + xx) % nx;
+      if (q == 0 || tid + kT < kNodes) {
+#pragma unroll
+        for (int m = 0; m < 6; ++m) nv[q][m] = g[(m >> 1) * (nz + 1) * P + (m & 1) * P];
+      }
     }
 #pragma unroll
-    for (int q = 0; q < kPer; ++q)
-      if (static_cast<int>(threadIdx.x) + q * kT < kNodes) vt[comp[q]][dz[q]][yy[q]][xx[q]] = nv[q];
+    for (int q = 0; q < 2; ++q) {
+      if (tid + q * kT < kW * kW) {
+#pragma unroll
+        for (int n = 0; n < 6; ++n) tl[n * kW * (kW + 1) + at[q]] = sv[n][q];
+      }
+      if (tid + q * kT < kNodes) {
+#pragma unroll
+        for (int m = 0; m < 6; ++m) pool[m * (kTile + 1) * (kTile + 2) + nat[q]] = nv[q][m];
+      }
+    }
   }
+  double zv[4];
+  fetch_z(0, zv);
   __syncthreads();
   const int ci = c.i - i0, cj = c.j - j0;  // the cell within the tile (clamped cells included)
   auto corner = [&](int cmp, int ez, int ey, int ex) { return vt[cmp][ez][cj + ey][ci + ex]; };
   double L[3][3], S[3][3], u[3];
   cell_gradient_from(corner, 0.25 / a.h, L);
   cell_velocity_from(corner, u);
+  __syncthreads();  // the corner nodes make way for the advection terms
+  const double* mine = tl + (ly + 2) * (kW + 1) + lx + 2;
 #pragma unroll 1
   for (int n = 0; n < 6; ++n) {
-    __syncthreads();  // the previous component's reads of tl (at n = 0: of the corner nodes) are done
-    tl[threadIdx.x / kW][threadIdx.x % kW] = sv[0];
-    if (second) tl[(threadIdx.x + kT) / kW][(threadIdx.x + kT) % kW] = sv[1];
     double z[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) z[q] = zv[q];
-    __syncthreads();
-    if (n < 5) fetch(n + 1, sv, zv);  // in flight while component n is computed
-    const double* row = &tl[ly + 2][lx + 2];
-    const double f0 = row[0];
-    const double dx = eno_2h(row[-2], row[-1], f0, row[1], row[2], u[0]);
-    const double dy = eno_2h(tl[ly][lx + 2], tl[ly + 1][lx + 2], f0, tl[ly + 3][lx + 2],
-                             tl[ly + 4][lx + 2], u[1]);
-    const double dz = eno_2h(z[0], z[1], f0, z[2], z[3], u[2]);
-    advs[n][threadIdx.x] = (u[0] * dx + u[1] * dy + u[2] * dz) * ih2;
-    fcell[n][threadIdx.x] = f0;
+    if (n < 5) fetch_z(n + 1, zv);  // in flight while component n is computed
+    const double* f = mine + n * kW * (kW + 1);
+    const double dx = eno_2h(f[-2], f[-1], f[0], f[1], f[2], u[0]);
+    const double dy = eno_2h(f[-2 * (kW + 1)], f[-(kW + 1)], f[0], f[kW + 1], f[2 * (kW + 1)], u[1]);
+    const double dz = eno_2h(z[0], z[1], f[0], z[2], z[3], u[2]);
+    advs[n][tid] = (u[0] * dx + u[1] * dy + u[2] * dz) * ih2;  // read back by this thread alone
   }
   if (!active) return;
 #pragma unroll
   for (int n = 0; n < 6; ++n) {
-    const double val = fcell[n][threadIdx.x];
+    const double val = mine[n * kW * (kW + 1)];
     S[VA[n]][VB[n]] = val;
     S[VB[n]][VA[n]] = val;
   }
-  stz_update<DIFF, true>(sigma, chi, sstar, chi1, Dcell, nx, ny, nz, c, t, L, S, chi[t],
-                         [&](int n) { return advs[n][threadIdx.x]; }, a);
+  stz_update<DIFF, true, EXPL>(sigma, chi, sstar, chi1, Dcell, nx, ny, nz, c, t, L, S, chi[t],
+                               [&](int n) { return advs[n][tid]; }, a);
+}
+
+constexpr int kPool = 6 * (kTile + 1) * (kTile + 2);
+static_assert(kPool >= 6 * kT, "the advection terms fit over the corner nodes");
+
+template <bool DIFF>
+__global__ __launch_bounds__(kT) void k_stz_step_adv(const double* __restrict__ v,
+                                                     const double* __restrict__ sigma,
+                                                     const double* __restrict__ chi,
+                                                     double* __restrict__ sstar,
+                                                     double* __restrict__ chi1,
+                                                     const double* __restrict__ Dcell, int nx, int ny,
+                                                     int nz, int ntx, int bands, int kz, StzArgs a) {
+  __shared__ double tl[kStage];
+  __shared__ double pool[kPool];
+  advected_tile<DIFF, false>(blockIdx.x, v, sigma, chi, sstar, chi1, Dcell, nx, ny, nz, ntx, bands, kz, a, tl,
+                             pool);
 }
 
 // Node divergence of a cell field (corner form of Eq. stag_stenc): for
@@ -567,17 +604,26 @@ __device__ __forceinline__ double node_diff(const double g[2][2][2], int b) {
 //   v' = v + dt ((D_h sigma)/rho - (v . grad) v + kappa lap v),
 // all from step n: D_h sigma as in k_rhs, the Laplacian by Eq. col_snd_deriv,
 // the advection by Eq. ENO with the node's own velocity (ghost node past a
-// wall: 2 v_wall - v of the node inside it).  Writes interior nodes of vout.
-__global__ __launch_bounds__(256) void k_explicit_velocity(const double* __restrict__ v,
-                                                           const double* __restrict__ sigma,
-                                                           double* __restrict__ vout, int nx, int ny,
-                                                           int nz, double h, double dt, double rho,
-                                                           double kappa) {
+// wall: 2 v_wall - v of the node inside it).  Thread t below the interior nodes'
+// count takes one of them, the 2 nx ny threads after those the wall nodes of
+// vout, at (-U, 0, 0) and (U, 0, 0).
+__device__ __forceinline__ void explicit_velocity(int t, const double* __restrict__ v,
+                                                  const double* __restrict__ sigma,
+                                                  double* __restrict__ vout, int nx, int ny, int nz,
+                                                  double h, double dt, double U, double rho,
+                                                  double kappa) {
   int i, j, k;
   NodeCells nc;
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (!node_of(t, nx, ny, nz, &i, &j, &k, &nc)) return;
   const int N = nx * ny * nz, P = nx * ny, C = (nz + 1) * P;
+  if (!node_of(t, nx, ny, nz, &i, &j, &k, &nc)) {
+    const int w = t - P * (nz - 1);
+    if (w >= 2 * P) return;
+    const int o = w < P ? w : nz * P + w - P;
+    vout[o] = w < P ? -U : U;
+    vout[C + o] = 0.0;
+    vout[2 * C + o] = 0.0;
+    return;
+  }
   double div[3] = {0.0, 0.0, 0.0};
 #pragma unroll
   for (int n = 0; n < 6; ++n) {
@@ -622,6 +668,50 @@ __global__ __launch_bounds__(256) void k_explicit_velocity(const double* __restr
     const double acc = (div[a] * (0.25 / h)) / rho - adv + kappa * lap;
     vout[a * C + o] = g[2] + dt * acc;
   }
+}
+
+// A step of the explicit method in one launch: the first `tiles` workgroups
+// take the stress and chi (as k_stz_step_adv, with the elastic stress added),
+// the others the velocity; all read step n and write the new state elsewhere.
+// On a 64 x 64 x 32 grid either part is a few workgroups per CU and bound by
+// the latency of its loads, and the step by its launches: 47.9 us in seven
+// (stress, velocity, walls, elastic stress, copies), 31.3 us in this one and the
+// copy back; 175 -> 143 us at 128 x 128 x 64.
+template <bool DIFF>
+__global__ __launch_bounds__(kT, 3) void k_explicit_step(const double* __restrict__ v,
+                                                      const double* __restrict__ sigma,
+                                                      const double* __restrict__ chi,
+                                                      double* __restrict__ vout,
+                                                      double* __restrict__ sout,
+                                                      double* __restrict__ chiout,
+                                                      const double* __restrict__ Dcell, int nx, int ny,
+                                                      int nz, int ntx, int bands, int kz, int tiles, StzArgs a,
+                                                      double U, double rho, double kappa) {
+  __shared__ double tl[kStage];
+  __shared__ double pool[kPool];
+  const int w = blockIdx.x;
+  if (w < tiles)
+    advected_tile<DIFF, true>(w, v, sigma, chi, sout, chiout, Dcell, nx, ny, nz, ntx, bands, kz, a, tl, pool);
+  else
+    explicit_velocity((w - tiles) * kT + threadIdx.x, v, sigma, vout, nx, ny, nz, a.h, a.dt, U, rho,
+                      kappa);
+}
+
+// The new state back into (v, sigma, chi): nc cells, nv values of v.
+__global__ __launch_bounds__(256) void k_copy_state(const double* __restrict__ v,
+                                                    const double* __restrict__ sigma,
+                                                    const double* __restrict__ chi,
+                                                    double* __restrict__ vout,
+                                                    double* __restrict__ sout,
+                                                    double* __restrict__ chiout, unsigned nc,
+                                                    unsigned nv) {
+  const unsigned stride = gridDim.x * blockDim.x, t0 = blockIdx.x * blockDim.x + threadIdx.x;
+#pragma unroll 4
+  for (unsigned t = t0; t < 6 * nc; t += stride) sout[t] = sigma[t];
+#pragma unroll 4
+  for (unsigned t = t0; t < nv; t += stride) vout[t] = v[t];
+#pragma unroll 2
+  for (unsigned t = t0; t < nc; t += stride) chiout[t] = chi[t];
 }
 
 // b = scale * D_h sigma* at the interior nodes (staggered divergence, the
@@ -953,6 +1043,31 @@ inline int blocks_for(long long n, int bs) { return static_cast<int>((n + bs - 1
 
 }  // namespace
 
+namespace {
+
+// The tiles of k_stz_step_adv: ntx along x, `bands` of 16 rows, planes in
+// segments of kz, as many as make (band, segment) units a multiple of the eight
+// XCDs (with whole bands alone 64 rows used four XCDs and 192 rows left four of
+// them idle a third of the time).
+struct AdvGrid {
+  int ntx, bands, kz;
+  unsigned wgs;
+};
+
+AdvGrid adv_grid(Dims d) {
+  AdvGrid g;
+  g.ntx = (d.nx + kTile - 1) / kTile;
+  g.bands = (d.ny + kTile - 1) / kTile;
+  int segs = 1;
+  while (g.bands * segs % 8 && segs < d.nz) segs *= 2;
+  g.kz = (d.nz + segs - 1) / segs;
+  const int units = g.bands * ((d.nz + g.kz - 1) / g.kz);
+  g.wgs = 8u * ((units + 7) / 8) * g.kz * g.ntx;
+  return g;
+}
+
+}  // namespace
+
 void launch_stz_step(const double* v, const double* sigma, const double* chi, double* sstar,
                      double* chi1, double* dcell, Dims d, const StzArgs& a, hipStream_t s) {
   const long long n = static_cast<long long>(d.nx) * d.ny * d.nz;
@@ -961,18 +1076,16 @@ void launch_stz_step(const double* v, const double* sigma, const double* chi, do
   if (a.l2 > 0.0)
     hipLaunchKernelGGL(k_dpl_cells, grid, block, 0, s, sigma, chi, dcell, static_cast<int>(n), a);
   if (a.advect) {
-    // z-segments of 32 cell planes, fewer when that leaves too few workgroups
-    // one workgroup per (16 x 16 tile, plane); bands of 16 rows dealt
-    // round-robin to the eight XCDs, each band plane by plane on its XCD
-    const int ntx = (d.nx + kTile - 1) / kTile, bands = (d.ny + kTile - 1) / kTile;
-    const long long wgs = 8LL * ((bands + 7) / 8) * d.nz * ntx;
-    const dim3 g2(static_cast<unsigned>(wgs)), b2(kTile * kTile);
+    // one workgroup per (16 x 16 tile, plane); bands of 16 rows by segments of
+    // planes dealt round-robin to the eight XCDs, each plane by plane on its XCD
+    const AdvGrid g = adv_grid(d);
+    const dim3 g2(g.wgs), b2(kT);
     if (a.l2 > 0.0)
       hipLaunchKernelGGL((k_stz_step_adv<true>), g2, b2, 0, s, v, sigma, chi, sstar, chi1, dcell,
-                         d.nx, d.ny, d.nz, ntx, bands, a);
+                         d.nx, d.ny, d.nz, g.ntx, g.bands, g.kz, a);
     else
       hipLaunchKernelGGL((k_stz_step_adv<false>), g2, b2, 0, s, v, sigma, chi, sstar, chi1, dcell,
-                         d.nx, d.ny, d.nz, ntx, bands, a);
+                         d.nx, d.ny, d.nz, g.ntx, g.bands, g.kz, a);
   } else if (a.l2 > 0.0) {
     hipLaunchKernelGGL((k_stz_step<true>), grid, block, 0, s, v, sigma, chi, sstar, chi1, dcell,
                        d.nx, d.ny, d.nz, a);
@@ -1003,11 +1116,30 @@ void launch_stress_update(const double* sstar, const double* v, double* out, Dim
                      d.nx, d.ny, d.nz, h, dt, lam, mu);
 }
 
-void launch_explicit_velocity(const double* v, const double* sigma, double* vout, Dims d, double h,
-                              double dt, double rho, double kappa, hipStream_t s) {
-  const long long n = static_cast<long long>(d.nx) * d.ny * (d.nz - 1);
-  hipLaunchKernelGGL(k_explicit_velocity, dim3(blocks_for(n, 256)), dim3(256), 0, s, v, sigma, vout,
-                     d.nx, d.ny, d.nz, h, dt, rho, kappa);
+void launch_explicit_step(const double* v, const double* sigma, const double* chi, double* vout,
+                          double* sout, double* chiout, double* dcell, Dims d, const StzArgs& a,
+                          double U, double rho, double kappa, hipStream_t s) {
+  const int n = d.nx * d.ny * d.nz;
+  if (a.l2 > 0.0)
+    hipLaunchKernelGGL(k_dpl_cells, dim3(blocks_for(n, 256)), dim3(256), 0, s, sigma, chi, dcell, n, a);
+  const AdvGrid g = adv_grid(d);
+  const int tiles = static_cast<int>(g.wgs);
+  const dim3 grid(g.wgs + blocks_for(static_cast<long long>(d.plane()) * (d.nz + 1), kT)), block(kT);
+  if (a.l2 > 0.0)
+    hipLaunchKernelGGL((k_explicit_step<true>), grid, block, 0, s, v, sigma, chi, vout, sout, chiout,
+                       dcell, d.nx, d.ny, d.nz, g.ntx, g.bands, g.kz, tiles, a, U, rho, kappa);
+  else
+    hipLaunchKernelGGL((k_explicit_step<false>), grid, block, 0, s, v, sigma, chi, vout, sout, chiout,
+                       dcell, d.nx, d.ny, d.nz, g.ntx, g.bands, g.kz, tiles, a, U, rho, kappa);
+}
+
+void launch_copy_state(const double* v, const double* sigma, const double* chi, double* vout,
+                       double* sout, double* chiout, Dims d, hipStream_t s) {
+  const unsigned nc = static_cast<unsigned>(d.nx) * d.ny * d.nz;
+  // four stress values per thread, up to 16 workgroups per CU
+  const int nb = std::min(4096, blocks_for(6LL * nc, 4 * 256));
+  hipLaunchKernelGGL(k_copy_state, dim3(nb), dim3(256), 0, s, v, sigma, chi, vout, sout, chiout, nc,
+                     static_cast<unsigned>(d.elems()));
 }
 
 void launch_set_walls(double* v, Dims d, double U, hipStream_t s) {
