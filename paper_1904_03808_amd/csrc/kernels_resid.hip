@@ -215,10 +215,12 @@ ZmArgs zm_args(Dims d) {
 constexpr int FX = 64, FY = 8;                      // fine tile
 constexpr int RXN = FX + 1, RYN = FY + 1, RN = RXN * RYN;  // residual patch
 constexpr int XXN = FX + 3, XYN = FY + 3, XN = XXN * XYN;  // x patch
-// Coarse planes per segment (at most); cut for small grids as the residual's
-// are (75.7 -> 10.7 us at 32^3, 87 -> 36 us at 96^3 in FP64) until one round of
-// resident workgroups is reached: two per CU by LDS in FP64, four in FP32.
-constexpr int kRrSeg = 16;
+// Coarse planes per segment, at most.  A segment of n marches 2 n + 1 fine planes
+// and fills its ring first (about three more); taken is the length with the
+// fewest plane steps over all rounds of resident workgroups (two per CU by LDS in
+// FP64, four in FP32), which small grids need shorter than large ones: 75.7 ->
+// 10.7 us at 32^3, 87 -> 27 us at 96^3 in FP64 against segments of 16.
+constexpr int kRrSeg = 32;
 
 struct RrArgs {
   int nx, ny, nz;
@@ -257,16 +259,23 @@ __global__ __launch_bounds__(256) void k_resid_restrict(const T* __restrict__ x,
     const int gj = (j0 - 2 + hy + 2 * ny) % ny, gi = (i0 - 2 + hx + 2 * nx) % nx;
     hoff[u] = static_cast<size_t>(gj) * nx + gi;
   }
-  // residual patch node e -> plane offset and position in the x patch
+  // residual patch: wavefront w takes rows w, w + 4 (w = 0 also row 8), a lane a
+  // column, and wavefront 1 the last column, a lane a row: a wavefront then reads
+  // consecutive words of the ring
+  const int lane = tid & 63, wave = tid >> 6;
   size_t roff[3];
-  int rpos[3];
+  int rpos[3], rat[3];
+  bool has[3];
 #pragma unroll
   for (int u = 0; u < 3; ++u) {
-    const int e = min(tid + u * 256, RN - 1);
-    const int ry = e / RXN, rx = e - ry * RXN;
+    const bool last = u == 2 && wave == 1;
+    has[u] = u < 2 || wave == 0 || (last && lane < RYN);
+    const int ry = u < 2 ? wave + 4 * u : (wave == 0 ? 8 : min(lane, RYN - 1));
+    const int rx = last ? RXN - 1 : lane;
     const int gj = (j0 - 1 + ry + ny) % ny, gi = (i0 - 1 + rx + nx) % nx;
     roff[u] = static_cast<size_t>(gj) * nx + gi;
     rpos[u] = (ry + 1) * XXN + rx + 1;
+    rat[u] = ry * RXN + rx;
   }
   T pre[3][3];
   auto fetch = [&](int p) {
@@ -289,7 +298,7 @@ __global__ __launch_bounds__(256) void k_resid_restrict(const T* __restrict__ x,
   auto fetch_b = [&](int p, T out[3][3]) {
 #pragma unroll
     for (int u = 0; u < 3; ++u)
-      if (tid + u * 256 < RN)
+      if (has[u])
 #pragma unroll
         for (int c = 0; c < 3; ++c)
           out[u][c] = __builtin_nontemporal_load(b + c * C + static_cast<size_t>(p) * P + roff[u]);
@@ -319,8 +328,8 @@ __global__ __launch_bounds__(256) void k_resid_restrict(const T* __restrict__ x,
     // residual on the patch
 #pragma unroll
     for (int u = 0; u < 3; ++u) {
-      const int e = tid + u * 256;
-      if (e < RN) {
+      const int e = rat[u];
+      if (has[u]) {
         const int pc = kf % 3, pm = (kf + 2) % 3, pp = (kf + 1) % 3;
         const int q = rpos[u];
 #define X(c, pl, dy, dx) ring[((pl) * 3 + (c)) * XN + q + (dy) * XXN + (dx)]
@@ -389,9 +398,18 @@ RrArgs rr_args(Dims d, int slots) {
   a.nz = d.nz;
   a.ntx = (d.nx + FX - 1) / FX;
   a.nty = (d.ny + FY - 1) / FY;
-  a.seg = kRrSeg;
-  while (a.seg > 1 && a.ntx * a.nty * ((d.nz / 2 - 1 + a.seg - 1) / a.seg) < slots) a.seg /= 2;
-  a.nseg = (d.nz / 2 - 1 + a.seg - 1) / a.seg;
+  const int planes = d.nz / 2 - 1;
+  long long best = 1LL << 60;
+  a.seg = 1;
+  for (int seg = std::min(kRrSeg, planes); seg >= 1; --seg) {
+    const long long wgs = 1LL * a.ntx * a.nty * ((planes + seg - 1) / seg);
+    const long long cost = (wgs + slots - 1) / slots * (2 * seg + 4);
+    if (cost < best) {
+      best = cost;
+      a.seg = seg;
+    }
+  }
+  a.nseg = (planes + a.seg - 1) / a.seg;
   a.real_wgs = a.ntx * a.nty * a.nseg;
   a.grid_per_xcd = (a.real_wgs + 7) / 8;
   return a;
