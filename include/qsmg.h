@@ -33,9 +33,10 @@
  *
  * Streams.  All work is enqueued on the stream given to qs_setup() (a
  * hipStream_t passed as void*; NULL = default stream).  Entry points that
- * return host-visible results (qs_mg_solve, qs_projection_step) wait for that
- * stream once per V-cycle (the calling thread polls it) to read the residual
- * norm; the others are asynchronous.  Calls on one handle must not overlap.
+ * return host-visible results (qs_mg_solve, qs_projection_step) wait once
+ * per V-cycle (the calling thread polls) for the residual norm and return when
+ * the last one is there and the stream idle (but for an FP32-IR solve's copy of
+ * the iterate into x); the others are asynchronous.  Calls on one handle must not overlap.
  *
  * Errors.  Every entry point returns a qs_status; nothing is thrown and the
  * process is never aborted.  On QS_ERR_HIP the stream may hold partial work.

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdint>
 #include <cstdio>
@@ -102,8 +103,9 @@ struct qs_handle {
   double* partial = nullptr;
   int partial_n = 0;
   double* dnorm = nullptr;   // device, 4 doubles
-  double* pinned = nullptr;      // host pinned, 4 doubles
+  double* pinned = nullptr;      // host pinned, 4 doubles: the norm, its ticket
   double* pinned_dev = nullptr;  // the same memory as the device addresses it (null: copy instead)
+  double ticket = 0.0;       // of the last norm asked for
   bool row_sweep = false;    // colour order allows the row-parity sweep kernel
   size_t lds_limit = 0;      // bytes of LDS a workgroup may use
   void* static_scratch = nullptr;  // device address of `scratch` on this handle's device (or null)
@@ -209,20 +211,32 @@ qs_status launch_check() {
   return e == hipSuccess ? QS_OK : hip_fail("kernel launch", e);
 }
 
-// Read the reduced double written to hd->dnorm[0] (and, when the pinned
-// buffer is device-addressable, by the reduction kernel straight into it).
-// The host polls the stream rather than sleeping in a synchronisation, so the
-// next cycle is enqueued as soon as the norm is there.
+// The reduced double written to hd->dnorm[0] (and, when the pinned buffer is
+// device-addressable, by the reduction kernel straight into it, followed by the
+// ticket of this norm).  The host polls the ticket rather than sleeping in a
+// synchronisation or waiting for the whole stream: work enqueued behind the
+// reduction runs meanwhile.  The stream is asked now and then, so that a failure
+// ends the wait.
 qs_status read_norm(qs_handle* hd, double* out) {
   QS_HIP(hipGetLastError());
   if (!hd->pinned_dev)
     QS_HIP(hipMemcpyAsync(hd->pinned, hd->dnorm, sizeof(double), hipMemcpyDeviceToHost, hd->stream));
-  hipError_t q;
-  while ((q = hipStreamQuery(hd->stream)) == hipErrorNotReady) {
+  const volatile double* p = hd->pinned;
+  for (unsigned n = 1;; ++n) {
+    if (hd->pinned_dev && p[1] == hd->ticket) break;
+    if (hd->pinned_dev && n % 64) continue;
+    const hipError_t q = hipStreamQuery(hd->stream);
+    if (q == hipErrorNotReady) continue;
+    QS_HIP(q);
+    break;
   }
-  QS_HIP(q);
-  *out = static_cast<volatile double*>(hd->pinned)[0];
+  std::atomic_thread_fence(std::memory_order_acquire);
+  *out = p[0];
   return QS_OK;
+}
+
+void reduce_norm(qs_handle* hd, int nb) {
+  launch_reduce_sum(hd->partial, nb, hd->dnorm, hd->pinned_dev, ++hd->ticket, hd->stream);
 }
 
 // ---- level operations in working precision T ----------------------------
@@ -298,16 +312,11 @@ void coarse_solve(qs_handle* hd, int l, T* x, const T* b, T* tmp) {
   launch_coarse_solve<T>(hd->Ainv, hd->ncoarse, rhs, x, lb.d, hd->stream);
 }
 
-// Copy the two wall planes of x into y (both buffers must carry them).
+// Copy the two wall planes of x into y (both buffers must carry them): one
+// launch instead of six copies of about 4 us.
 template <typename T>
 void copy_walls(const T* x, T* y, Dims d, hipStream_t s) {
-  const size_t P = static_cast<size_t>(d.plane());
-  for (int c = 0; c < 3; ++c) {
-    const size_t o0 = static_cast<size_t>(c) * d.comp();
-    const size_t o1 = o0 + static_cast<size_t>(d.nz) * P;
-    (void)hipMemcpyAsync(y + o0, x + o0, P * sizeof(T), hipMemcpyDeviceToDevice, s);
-    (void)hipMemcpyAsync(y + o1, x + o1, P * sizeof(T), hipMemcpyDeviceToDevice, s);
-  }
+  launch_copy_walls_of<T>(x, y, d, s);
 }
 
 template <typename T>
@@ -326,6 +335,36 @@ bool use_row_sweep(qs_handle* hd, int l) {
   return l == 0 && hd->row_sweep && sweep_supported(hd->L[l].d, hd->lds_limit, sizeof(T));
 }
 
+// One sweep of the fine level by tiles, from src into dst.
+template <typename T>
+void tile_sweep(qs_handle* hd, LevelBufs& lb, const T* src, T* dst, const T* b, int tr, int halves,
+                bool reverse, bool zero) {
+  const FineCoef<T>& cf = Prec<T>::fc(hd);
+  const int rp0 = reverse ? 1 : 0;
+  launch_sweep_tile<T>(src, src, dst, b, lb.d, tr, halves, rp0, reverse, zero ? 2 : 0, cf, hd->stream);
+  if (halves == 1)
+    launch_sweep_tile<T>(src, dst, dst, b, lb.d, tr, 1, 1 - rp0, reverse, zero ? 1 : 0, cf, hd->stream);
+}
+
+// The first pre-smoothing sweep of an FP64 cycle on the fine level, enqueued before
+// it is known whether the cycle is needed, so that the GPU has work while the host
+// reads the residual norm.  It only writes the second smoother buffer: x is
+// untouched if the cycle is not run.  Done where the tile sweep serves, whose 9 to
+// 100 us cover the host's wait (32^3, a solve of 22 cycles: 1755 us without this and
+// the ticket, 1536 with; gradient through 96^3 grids: 38121 and 37736); on larger
+// grids the sweep wasted at the end costs more than the waits, and FP32 refinement
+// reads a norm only every few cycles (64x64x32 with it 2742 us, without 2629).
+bool begin_smooth(qs_handle* hd, const double* x, const double* b) {
+  LevelBufs& lb = hd->L[0];
+  int halves = 0;
+  if (!hd->pinned_dev || hd->nlev < (hd->bottom ? 3 : 2) || hd->p.n_pre < 1 || !use_row_sweep<double>(hd, 0))
+    return false;
+  const int tr = sweep_tile_rows(lb.d, hd->lds_limit, sizeof(double), &halves);
+  if (tr <= 0) return false;
+  tile_sweep<double>(hd, lb, x, lb.y64, b, tr, halves, false, false);
+  return true;
+}
+
 // `sweeps` Gauss-Seidel sweeps on level l, in the colour order given at
 // setup (forward) or its reverse.  The row-parity kernel ping-pongs between
 // x and the level's second buffer; an odd sweep count ends with a copy back.
@@ -335,9 +374,10 @@ bool use_row_sweep(qs_handle* hd, int l) {
 // prolong: the coarse correction of level l + 1 (reverse sweeps by the row
 // kernel only, not by tiles): the first sweep adds x += T prolong on the fly
 // instead of a separate prolongation.
+// begun: the first sweep has been enqueued already (begin_smooth).
 template <typename T>
 void smooth(qs_handle* hd, int l, T* x, const T* b, int sweeps, bool reverse,
-            bool x_zero = false, const T* prolong = nullptr) {
+            bool x_zero = false, const T* prolong = nullptr, bool begun = false) {
   if (sweeps <= 0) return;
   LevelBufs& lb = hd->L[l];
   const int* ord = hd->p.colour_order;
@@ -366,14 +406,13 @@ void smooth(qs_handle* hd, int l, T* x, const T* b, int sweeps, bool reverse,
   const int rp0 = reverse ? 1 : 0, pf = reverse ? 1 : 0, xf = reverse ? 1 : 0;
   int halves = 0;
   const int tr = sweep_tile_rows(lb.d, hd->lds_limit, sizeof(T), &halves);
-  for (int s = 0; s < sweeps; ++s) {
+  if (begun) std::swap(cur, oth);
+  for (int s = begun ? 1 : 0; s < sweeps; ++s) {
     const bool z = x_zero && s == 0 && !reverse;
     const bool pro = prolong && s == 0 && reverse;
     const T* ec = pro ? prolong : nullptr;
     if (tr > 0) {
-      launch_sweep_tile<T>(cur, cur, oth, b, lb.d, tr, halves, rp0, reverse, z ? 2 : 0, cf, hd->stream);
-      if (halves == 1)
-        launch_sweep_tile<T>(cur, oth, oth, b, lb.d, tr, 1, 1 - rp0, reverse, z ? 1 : 0, cf, hd->stream);
+      tile_sweep<T>(hd, lb, cur, oth, b, tr, halves, reverse, z);
       std::swap(cur, oth);
       continue;
     }
@@ -390,9 +429,9 @@ void smooth(qs_handle* hd, int l, T* x, const T* b, int sweeps, bool reverse,
 }
 
 // x_zero: x is zero on entry and need not hold it (see smooth; only when the
-// row sweep smooths level l and n_pre >= 1)
+// row sweep smooths level l and n_pre >= 1); begun: see smooth
 template <typename T>
-void vcycle(qs_handle* hd, int l, T* x, const T* b, bool x_zero = false) {
+void vcycle(qs_handle* hd, int l, T* x, const T* b, bool x_zero = false, bool begun = false) {
   LevelBufs& lb = hd->L[l];
   if (l == hd->nlev - 1) {
     coarse_solve<T>(hd, l, x, b, Prec<T>::r(lb));
@@ -402,7 +441,7 @@ void vcycle(qs_handle* hd, int l, T* x, const T* b, bool x_zero = false) {
     launch_bottom<T>(hd->bottom_M, hd->bottom_tw, b, x, hd->bottom_yh, lb.d, hd->stream);
     return;
   }
-  smooth<T>(hd, l, x, b, hd->p.n_pre, false, x_zero);
+  smooth<T>(hd, l, x, b, hd->p.n_pre, false, x_zero, nullptr, begun);
   LevelBufs& cb = hd->L[l + 1];
   // the restriction also clears the interior of the coarse correction (its
   // walls are zero from setup and never written)
@@ -448,7 +487,7 @@ int residual_norm0(qs_handle* hd, const double* x, const double* b, Tout* r, dou
                                                hd->partial, hd->stream)
           : launch_residual_fine_zm<double, Tout>(x, b, r, hd->L[0].d, hd->fc64, scale,
                                                   hd->partial, hd->stream);
-  launch_reduce_sum(hd->partial, nb, hd->dnorm, hd->pinned_dev, hd->stream);
+  reduce_norm(hd, nb);
   return nb;
 }
 
@@ -558,6 +597,7 @@ qs_status qs_setup(const qs_params* p, void* workspace, size_t workspace_bytes, 
       delete hd;
       return hip_fail("hipHostMalloc", e);
     }
+    std::fill_n(hd->pinned, 4, 0.0);  // no ticket yet
     void* dp = nullptr;
     if (hipHostGetDevicePointer(&dp, hd->pinned, 0) == hipSuccess && dp)
       hd->pinned_dev = static_cast<double*>(dp);
@@ -730,6 +770,11 @@ static qs_status solve_impl(qs_handle* hd, const double* b, double* x, double rt
   bool pending = false;  // a correction in l0.x32 not yet added to xs
   double e_scale = 0.0;
   auto finish = [&](qs_status st) {
+    // the caller finds the stream idle, but for the copy below
+    hipError_t q;
+    while ((q = hipStreamQuery(hd->stream)) == hipErrorNotReady) {
+    }
+    if (q != hipSuccess && st == QS_OK) st = hip_fail("hipStreamQuery", q);
     if (xs != x)
       (void)hipMemcpyAsync(x, xs, d0.elems() * sizeof(double), hipMemcpyDeviceToDevice,
                            hd->stream);
@@ -754,7 +799,7 @@ static qs_status solve_impl(qs_handle* hd, const double* b, double* x, double rt
         double* xn = xs == x ? l0.xalt64 : x;
         const int nb = launch_update_residual_zm(xs, l0.x32, e_scale, xn, b, l0.b32, d0, hd->fc64,
                                                  1.0 / scale_used, hd->partial, hd->stream);
-        launch_reduce_sum(hd->partial, nb, hd->dnorm, hd->pinned_dev, hd->stream);
+        reduce_norm(hd, nb);
         xs = xn;
         pending = false;
       } else {
@@ -763,6 +808,7 @@ static qs_status solve_impl(qs_handle* hd, const double* b, double* x, double rt
     } else if (need_norm) {
       residual_norm0<double>(hd, x, b, nullptr, 1.0, false);
     }
+    const bool begun = !ir && !fixed && cycles < max_cycles && begin_smooth(hd, x, b);
     if (need_norm) {
       double rn2 = 0.0;
       st = read_norm(hd, &rn2);
@@ -804,7 +850,7 @@ static qs_status solve_impl(qs_handle* hd, const double* b, double* x, double rt
       cycles += inner;
       inner_prev = inner;
     } else {
-      vcycle<double>(hd, 0, x, b);
+      vcycle<double>(hd, 0, x, b, false, begun);
       ++cycles;
     }
   }

@@ -139,14 +139,17 @@ void launch_restrict(const T* r, T* bc, T* xc, Dims fine, hipStream_t s);
 template <typename T>
 void launch_prolong_add(T* x, const T* ec, Dims fine, hipStream_t s);
 
-// Deterministic sum of partial[0..n) into out[0].
 // Sum of n partials in a fixed order into out[0] (device) and, if given,
-// out_host[0] (device address of pinned host memory).
-void launch_reduce_sum(const double* partial, int n, double* out, double* out_host,
+// out_host[0] (device address of pinned host memory), where out_host[1] becomes
+// `ticket` after it.
+void launch_reduce_sum(const double* partial, int n, double* out, double* out_host, double ticket,
                        hipStream_t s);
 
 template <typename T>
 void launch_fill(T* x, size_t n, T value, hipStream_t s);
+// The two wall planes of x into y.
+template <typename T>
+void launch_copy_walls_of(const T* x, T* y, Dims d, hipStream_t s);
 // Zero the interior planes of a node vector.
 template <typename T>
 void launch_zero_interior(T* x, Dims d, hipStream_t s);

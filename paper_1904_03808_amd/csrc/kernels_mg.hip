@@ -867,7 +867,7 @@ __global__ __launch_bounds__(256) void k_prolong_add(T* __restrict__ x, const T*
 
 __global__ __launch_bounds__(1024) void k_reduce_sum(const double* __restrict__ partial, int n,
                                                      double* __restrict__ out,
-                                                     double* __restrict__ out_host) {
+                                                     double* __restrict__ out_host, double ticket) {
   __shared__ double red[16];
   double s = 0.0;
   for (int q = threadIdx.x; q < n; q += blockDim.x) s += partial[q];
@@ -880,7 +880,11 @@ __global__ __launch_bounds__(1024) void k_reduce_sum(const double* __restrict__ 
     double t = 0.0;
     for (int w = 0; w < (int)(blockDim.x >> 6); ++w) t += red[w];
     out[0] = t;
-    if (out_host) out_host[0] = t;
+    if (out_host) {
+      out_host[0] = t;
+      __threadfence_system();  // the host reads the sum once it sees the ticket
+      reinterpret_cast<volatile double*>(out_host)[1] = ticket;
+    }
   }
 }
 
@@ -889,6 +893,17 @@ __global__ void k_fill(T* __restrict__ x, size_t n, T v) {
   size_t t = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x;
   const size_t stride = static_cast<size_t>(gridDim.x) * blockDim.x;
   for (; t < n; t += stride) x[t] = v;
+}
+
+// The two wall planes of x into y, all components (P nodes a plane).
+template <typename T>
+__global__ __launch_bounds__(256) void k_copy_walls_of(const T* __restrict__ x, T* __restrict__ y, int P,
+                                                       int nz) {
+  const int t = blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= 6 * P) return;
+  const int q = t / P;
+  const size_t o = (size_t)((q >> 1) * (nz + 1) + (q & 1) * nz) * P + (t - q * P);
+  y[o] = x[o];
 }
 
 // The coarsest solve in one launch: x_interior = A^-1 b_interior with the
@@ -1085,9 +1100,9 @@ void launch_prolong_add(T* x, const T* ec, Dims f, hipStream_t s) {
                        ec, f.nx, f.ny, f.nz, kseg);
 }
 
-void launch_reduce_sum(const double* partial, int n, double* out, double* out_host,
+void launch_reduce_sum(const double* partial, int n, double* out, double* out_host, double ticket,
                        hipStream_t s) {
-  hipLaunchKernelGGL(k_reduce_sum, dim3(1), dim3(1024), 0, s, partial, n, out, out_host);
+  hipLaunchKernelGGL(k_reduce_sum, dim3(1), dim3(1024), 0, s, partial, n, out, out_host, ticket);
 }
 
 template <typename T>
@@ -1097,6 +1112,12 @@ void launch_fill(T* x, size_t n, T value, hipStream_t s) {
   hipLaunchKernelGGL(k_fill<T>, dim3(nb), dim3(256), 0, s, x, n, value);
 }
 
+
+template <typename T>
+void launch_copy_walls_of(const T* x, T* y, Dims d, hipStream_t s) {
+  hipLaunchKernelGGL(k_copy_walls_of<T>, dim3(blocks_for(6LL * d.plane(), 256)), dim3(256), 0, s, x, y,
+                     d.plane(), d.nz);
+}
 
 template <typename T>
 void launch_zero_interior(T* x, Dims d, hipStream_t s) {
@@ -1122,6 +1143,7 @@ void launch_coarse_solve(const double* Ainv, int n, const T* b, T* x, Dims d, hi
   template void launch_restrict<T>(const T*, T*, T*, Dims, hipStream_t);                         \
   template void launch_prolong_add<T>(T*, const T*, Dims, hipStream_t);                          \
   template void launch_fill<T>(T*, size_t, T, hipStream_t);                                      \
+  template void launch_copy_walls_of<T>(const T*, T*, Dims, hipStream_t);                        \
   template void launch_zero_interior<T>(T*, Dims, hipStream_t);                                  \
   template void launch_coarse_solve<T>(const double*, int, const T*, T*, Dims, hipStream_t);
 QS_INST(double)

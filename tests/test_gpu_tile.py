@@ -64,3 +64,20 @@ def test_zero_start(n, coarse):
         g.solve(torch.from_numpy(b).cuda(), xd, rtol=1e-10)
         r = o.residual(xd.cpu().numpy(), b)
         assert np.linalg.norm(r) <= 1.01e-10 * o.lifted_rhs_norm(b, x)
+
+
+@pytest.mark.parametrize("n,coarse", [((34, 6, 10), 5), ((96, 96, 24), 3)])
+def test_sweep_before_norm(n, coarse):
+    """A solve to a tolerance, which enqueues the first sweep of a cycle before it
+    reads the norm, gives the iterate of the same number of cycles run without
+    norms, bit for bit, also where the last of those sweeps is not needed."""
+    g, _ = pair(n, coarse, "fp64")
+    nx, ny, nz = n
+    rng = np.random.default_rng(7)
+    x0 = torch.from_numpy(rng.standard_normal((3, nz + 1, ny, nx))).cuda()
+    b = torch.from_numpy(rng.standard_normal((3, nz + 1, ny, nx)) * nz * nz).cuda()
+    x, y = x0.clone(), x0.clone()
+    info = g.solve(b, x, rtol=1e-6)
+    assert info.cycles > 2
+    g.solve(b, y, rtol=0.0, max_cycles=info.cycles)
+    assert torch.equal(x, y)
