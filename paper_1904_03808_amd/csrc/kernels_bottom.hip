@@ -12,11 +12,16 @@
 // handle has, and are held and applied in FP64 in both precisions, as the
 // coarsest inverse is.
 //
+// The map commutes with the reflections in x and y as well, which keep every
+// node's colour.  Taken about the nodes' own positions (half a shift for the odd
+// columns and rows) and with the z component times i, a block is therefore real,
+// and the blocks of (mx, my) and (mx, -my) differ in the y component's sign only:
+// 6.5 MB at 8^3 under 16^3 where complex blocks of every mode are 17.6 MB.
+//
 // What bounds it: the cycle it stands for is 16 colour-pair launches, residual,
 // restriction, coarsest solve and correction, each a fixed cost of 3 to 7 us
-// and next to no work (8^3 under 16^3: 21 launches, 90 us).  The blocks are
-// about as many bytes as the dense coarsest inverse (17.6 MB against 14.5 MB
-// at 8^3), so the map costs about what that one product did.
+// and next to no work (8^3 under 16^3: 21 launches, 90 us).  The map costs about
+// what the coarsest inverse's product alone did.
 #include <hip/hip_runtime.h>
 
 #include "device.h"
@@ -59,9 +64,27 @@ __device__ __forceinline__ int mode_index(int mx, int my, int cx, int cy, bool* 
   return mx == 0 ? my : h + (mx - 1) * cy + my;
 }
 
+__host__ __device__ inline int block_count(int cx, int cy) { return (cx / 2 + 1) * half_y(cy); }
+
+// Position of the block that serves mode (mx, my).
+__device__ __forceinline__ int block_of(int mx, int my, int cx, int cy) {
+  return mx + (cx / 2 + 1) * (2 * my <= cy ? my : cy - my);
+}
+
+// Unknown u's factor between the transform at mode (mx, my) and the real blocks.
+__device__ __forceinline__ double2 real_factor(int u, int nz, int mx, int my, int cx, int cy) {
+  const int ex = u & 1, ey = (u >> 1) & 1, c = u / (4 * (nz - 1));
+  const int sy = 2 * my <= cy ? my : my - cy;
+  double sn, cs;
+  sincospi(static_cast<double>(mx * ex) / cx + static_cast<double>(sy * ey) / cy, &sn, &cs);
+  if (c == 2) return make_double2(sn, cs);  // i exp(-i a)
+  return c == 1 && sy < 0 ? make_double2(-cs, sn) : make_double2(cs, -sn);
+}
+
 // The transform of the node vector f (level dims nx, ny, nz) at mode (mx, my):
 // out[(c (nz-1) + k-1) 4 + 2 ey + ex] = sum over shifts of
-// f[c][k][2 sy + ey][2 sx + ex] exp(-2 pi i (mx sx / cx + my sy / cy)).
+// f[c][k][2 sy + ey][2 sx + ex] exp(-2 pi i (mx sx / cx + my sy / cy)),
+// times the factor of the real blocks.
 // y first (rows are read whole, coalesced in x), then x from LDS (part).
 template <typename T>
 __device__ __forceinline__ void forward_mode(const T* __restrict__ f, int nx, int ny, int nz, int mx,
@@ -104,7 +127,8 @@ __device__ __forceinline__ void forward_mode(const T* __restrict__ f, int nx, in
       ph += mx;
       if (ph >= cx) ph -= cx;
     }
-    out[u] = s;
+    const double2 w = real_factor(u, nz, mx, my, cx, cy);
+    out[u] = make_double2(s.x * w.x - s.y * w.y, s.x * w.y + s.y * w.x);
   }
   __syncthreads();
 }
@@ -118,11 +142,11 @@ __device__ __forceinline__ void load_twiddles(const double2* __restrict__ tw, in
 // One row slice of one mode's block applied to the transform of b, which every
 // slice forms itself (b is a few hundred KB and comes from L2): yh[mode][row].
 // A workgroup of 512 threads takes 32 rows and splits the columns over sixteen
-// groups; 32 consecutive rows of a column are one 512-byte access.  The
+// groups; 32 consecutive rows of a column are one 256-byte access.  The
 // transform's loads go out eight at a time (10.5 us at 8^3 under 16^3 in FP64
 // with one load after the other and 256 threads).
 template <typename T>
-__global__ __launch_bounds__(kThreads) void k_bottom_modes(const double2* __restrict__ M,
+__global__ __launch_bounds__(kThreads) void k_bottom_modes(const double* __restrict__ M,
                                                       const T* __restrict__ b, int nx, int ny, int nz,
                                                       const double2* __restrict__ tw,
                                                       double2* __restrict__ yh) {
@@ -139,12 +163,13 @@ __global__ __launch_bounds__(kThreads) void k_bottom_modes(const double2* __rest
   const int row = blockIdx.y * kRows + rr;
   double2 s = make_double2(0.0, 0.0);
   if (row < n) {
-    const double2* __restrict__ col = M + static_cast<size_t>(blockIdx.x) * n * n + row;
+    const double* __restrict__ col = M + static_cast<size_t>(block_of(mx, my, cx, cy)) * n * n + row;
 #pragma unroll 8
     for (int q = g; q < n; q += kGroups) {
-      const double2 a = col[static_cast<size_t>(q) * n], v = bh[q];
-      s.x += a.x * v.x - a.y * v.y;
-      s.y += a.x * v.y + a.y * v.x;
+      const double a = col[static_cast<size_t>(q) * n];
+      const double2 v = bh[q];
+      s.x += a * v.x;
+      s.y += a * v.y;
     }
   }
   part[threadIdx.x] = s;
@@ -155,7 +180,8 @@ __global__ __launch_bounds__(kThreads) void k_bottom_modes(const double2* __rest
       s.x += part[q * kRows + rr].x;
       s.y += part[q * kRows + rr].y;
     }
-    yh[static_cast<size_t>(blockIdx.x) * n + row] = s;
+    const double2 w = real_factor(row, nz, mx, my, cx, cy);
+    yh[static_cast<size_t>(blockIdx.x) * n + row] = make_double2(s.x * w.x + s.y * w.y, s.y * w.x - s.x * w.y);
   }
 }
 
@@ -218,10 +244,10 @@ __global__ __launch_bounds__(256) void k_bottom_unit(double* __restrict__ b, dou
   x[t] = 0.0;
 }
 
-// Column u of every mode's block from the response x to unit u.
+// Column u of every block from the response x to unit u.
 __global__ __launch_bounds__(kThreads) void k_bottom_column(const double* __restrict__ x, int nx, int ny,
                                                        int nz, const double2* __restrict__ tw, int u,
-                                                       double2* __restrict__ M) {
+                                                       double* __restrict__ M) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int cx = nx / 2, cy = ny / 2, n = 12 * (nz - 1);
   double2* ltw = reinterpret_cast<double2*>(smem);
@@ -229,10 +255,12 @@ __global__ __launch_bounds__(kThreads) void k_bottom_column(const double* __rest
   double2* part = xh + n;
   int mx, my;
   mode_of(blockIdx.x, cx, cy, &mx, &my);
+  if (2 * my > cy) return;  // the block of (mx, cy - my) serves
   load_twiddles(tw, cx, cy, ltw);
   forward_mode<double>(x, nx, ny, nz, mx, my, ltw, ltw + cx, part, xh);
-  double2* col = M + (static_cast<size_t>(blockIdx.x) * n + u) * n;
-  for (int t = threadIdx.x; t < n; t += blockDim.x) col[t] = xh[t];
+  double* col = M + (static_cast<size_t>(block_of(mx, my, cx, cy)) * n + u) * n;
+  const double2 w = real_factor(u, nz, mx, my, cx, cy);
+  for (int t = threadIdx.x; t < n; t += blockDim.x) col[t] = xh[t].x * w.x + xh[t].y * w.y;
 }
 
 size_t modes_lds(Dims d) {
@@ -251,7 +279,7 @@ int bottom_unknowns(Dims d) { return 12 * (d.nz - 1); }
 
 size_t bottom_matrix_values(Dims d) {
   const size_t n = static_cast<size_t>(bottom_unknowns(d));
-  return 2 * n * n * mode_count(d.nx / 2, d.ny / 2);
+  return n * n * block_count(d.nx / 2, d.ny / 2);
 }
 
 size_t bottom_vector_values(Dims d) {
@@ -263,8 +291,9 @@ size_t bottom_vector_values(Dims d) {
 // which the coarsest inverse streams.  The block size also bounds the setup
 // (one cycle per unknown).  The transforms stage their sums in LDS (64 KB).
 bool bottom_supported(Dims d) {
-  constexpr size_t kMaxBytes = 96ull << 20, kMaxLds = 64ull << 10;
-  return bottom_unknowns(d) <= 384 && bottom_matrix_values(d) * sizeof(double) <= kMaxBytes &&
+  constexpr size_t kMaxBytes = 48ull << 20, kMaxLds = 64ull << 10;
+  const size_t n = static_cast<size_t>(bottom_unknowns(d));
+  return n <= 384 && n * n * mode_count(d.nx / 2, d.ny / 2) * sizeof(double) <= kMaxBytes &&
          modes_lds(d) <= kMaxLds && back_lds(d) <= kMaxLds;
 }
 
@@ -277,8 +306,7 @@ void launch_bottom_unit(double* b, double* x, Dims d, int u, hipStream_t s) {
 
 void launch_bottom_column(const double* x, Dims d, const double* tw, int u, double* M, hipStream_t s) {
   hipLaunchKernelGGL(k_bottom_column, dim3(mode_count(d.nx / 2, d.ny / 2)), dim3(kThreads), modes_lds(d), s,
-                     x, d.nx, d.ny, d.nz, reinterpret_cast<const double2*>(tw), u,
-                     reinterpret_cast<double2*>(M));
+                     x, d.nx, d.ny, d.nz, reinterpret_cast<const double2*>(tw), u, M);
 }
 
 template <typename T>
@@ -286,8 +314,8 @@ void launch_bottom(const double* M, const double* tw, const T* b, T* x, double* 
                    hipStream_t s) {
   const int n = bottom_unknowns(d);
   hipLaunchKernelGGL(k_bottom_modes<T>, dim3(mode_count(d.nx / 2, d.ny / 2), (n + kRows - 1) / kRows),
-                     dim3(kThreads), modes_lds(d), s, reinterpret_cast<const double2*>(M), b, d.nx, d.ny,
-                     d.nz, reinterpret_cast<const double2*>(tw), reinterpret_cast<double2*>(yh));
+                     dim3(kThreads), modes_lds(d), s, M, b, d.nx, d.ny, d.nz,
+                     reinterpret_cast<const double2*>(tw), reinterpret_cast<double2*>(yh));
   hipLaunchKernelGGL(k_bottom_back<T>, dim3(3 * (d.nz - 1)), dim3(256), back_lds(d), s,
                      reinterpret_cast<const double2*>(yh), x, d.nx, d.ny, d.nz,
                      reinterpret_cast<const double2*>(tw));
