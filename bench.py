@@ -27,15 +27,15 @@ HBM_PEAK_GBS = 8000.0
 # HBM bytes per launch of the fine FP32 half sweep at 256^3, from two rocprofv3
 # counter runs of `bench.py --profile-smoother` (FETCH_SIZE, then WRITE_SIZE; KiB
 # per dispatch, mean of 6 launches).  A 512 MiB device copy reads as
-# FETCH_SIZE = 262,166 KiB and WRITE_SIZE = 524,288 KiB: on this chip every read
+# FETCH_SIZE = 262,162 KiB and WRITE_SIZE = 524,288 KiB: on this chip every read
 # request (TCC_EA0_RDREQ, 4,194,593 for the copy) carries 128 bytes but the
 # derived FETCH_SIZE prices it at 64, so reads scale by 2.0 and writes by 1.0.
 # Valid only for the kernel source these counters were taken on.
 SWEEP_COUNTERS = {
     "kernel_source": "paper_1904_03808_amd/csrc/kernels_sweep.hip",
-    "source_sha256_16": "dea4244a5a0518a8",
+    "source_sha256_16": "55bd611c49a70b24",
     "n": 256,
-    "fetch_kib": 177898.6,
+    "fetch_kib": 177902.2,
     "write_kib": 97920.0,
     "fetch_scale": 2.0,
     "write_scale": 1.0,
@@ -850,7 +850,7 @@ def main():
         "smoother": sm,
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
-                     "kernel": "k_sweep_rows<float, 256, 0, 0>: fine-level FP32 half sweep",
+                     "kernel": "k_sweep_rows<float, 260, 0, 0>: fine-level FP32 half sweep",
                      "copy_GBs": copy_gbs, "frac_of_copy": achieved / copy_gbs,
                      "algorithmic_bytes_per_launch": algo_bytes,
                      "bytes_per_node_update": 36,
