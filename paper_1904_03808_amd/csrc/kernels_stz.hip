@@ -337,7 +337,13 @@ __device__ __forceinline__ void stz_update(const double* __restrict__ sigma,
     // below the rounding from b = 20 on.
     const double take = 2.0 * a.mu * tau, grow = (tau / a.c0) * 2.0 / a.s_y;
     double xp = x, sb = sbar, drop = 0.0;  // drop: the part of the deviator taken off
-    for (int it = 0; it < M; ++it) {
+    // What is no number keeps its way through the step, decided here and not in
+    // the chain (a test of D there cost 1 %): D^pl = 0 times a NaN stress is NaN
+    // in chi, the NaN rate of a NaN chi leaves the stress alone, and an infinite
+    // chi is NaN after one sub-step.
+    if (!(sbar > a.s_y)) xp += grow * (sb * 0.0) * (a.chi_inf - xp);
+    const int steps = fabs(x) < HUGE_VAL ? M : (x == x ? 1 : 0);
+    for (int it = 0; it < steps; ++it) {
       if (!(sb > a.s_y)) break;  // at or below yield nothing changes any more
       const double b = a.beta * sb, is = 1.0 / sb;
       double e = 0.5 * exp(b - 1.0 / xp);
