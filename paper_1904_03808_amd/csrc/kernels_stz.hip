@@ -84,21 +84,29 @@ struct Plastic {
   double D, dD_ds, dD_dchi;
 };
 
-// cosh(b) and, for the derivative, sinh(b), b >= 0, from one exponential (two
-// below 20, where exp(-b) still counts; sinh by the library where the
-// difference would cancel).
+// exp(b) / 2 and exp(-b) / 2 for b >= 0: cosh(b) is their sum, sinh(b) their
+// difference (from 3 on, below which it would cancel).  Past 709 the first
+// comes from exp(b / 2), so that cosh is finite as far as the library's.
+__device__ __forceinline__ double half_exp(double b) {
+  const bool large = b > 709.0;
+  const double e = exp(large ? 0.5 * b : b);
+  return large ? (0.5 * e) * e : 0.5 * e;
+}
+
+// cosh(b) for any b; exp(-|b|) counts below 20.
 __device__ __forceinline__ double cosh_of(double b) {
-  const double e = exp(b);
-  return 0.5 * (b < 20.0 ? e + exp(-b) : e);
+  b = fabs(b);
+  const double e = half_exp(b);
+  return b < 20.0 ? e + 0.5 * exp(-b) : e;
 }
 
 __device__ __forceinline__ Plastic plastic_rate(double sbar, double chi, const StzArgs& a) {
   Plastic p{0.0, 0.0, 0.0};
   if (sbar > a.s_y) {
     const double A = exp(-1.0 / chi) * a.rate0;
-    const double bs = a.beta * sbar;
-    const double e = exp(bs), em = exp(-bs);
-    const double ch = 0.5 * (e + em), sh = bs > 1.0 ? 0.5 * (e - em) : sinh(bs);
+    const double bs = a.beta * sbar, b = fabs(bs);
+    const double e = half_exp(b), em = 0.5 * exp(-b);
+    const double ch = e + em, sh = copysign(b > 3.0 ? e - em : sinh(b), bs);
     const double f = 1.0 - a.s_y / sbar;
     p.D = A * ch * f;
     p.dD_ds = A * (a.beta * sh * f + ch * a.s_y / (sbar * sbar));
@@ -345,7 +353,7 @@ __device__ __forceinline__ void stz_update(const double* __restrict__ sigma,
     const int steps = fabs(x) < HUGE_VAL ? M : (x == x ? 1 : 0);
     for (int it = 0; it < steps; ++it) {
       if (!(sb > a.s_y)) break;  // at or below yield nothing changes any more
-      const double b = a.beta * sb, is = 1.0 / sb;
+      const double b = fabs(a.beta * sb), is = 1.0 / sb;
       double e = 0.5 * exp(b - 1.0 / xp);
       if (b < 20.0) e += e * exp(-2.0 * b);
       const double D = a.rate0 * e * (1.0 - a.s_y * is);

@@ -1,5 +1,5 @@
 """GPU parity of the STZ step on values out of the ordinary: NaN and infinities
-in the state."""
+in the state, arguments of cosh up to where it overflows, and negative ones."""
 import numpy as np
 import pytest
 
@@ -58,3 +58,50 @@ def test_nan_in_substeps(n_sub):
     largest = np.nan_to_num(np.abs(rs)).max(axis=0)  # of the cell (one overshoots far)
     assert np.all(np.nan_to_num(np.abs(ss - rs)) <= 1e-12 * largest)
     assert np.nanmax(np.abs(c1 - rc)) <= 1e-11 * np.abs(rc - chi)[np.isfinite(rc)].max() + 1e-16
+
+
+@pytest.mark.parametrize("sign", [1, -1])
+@pytest.mark.parametrize("n_sub", [1, -2])
+def test_largest_arguments(sign, n_sub):
+    """beta sbar between 709.8, where exp overflows, and 710.4, where cosh does not
+    yet, and its negative.  The argument carries a few roundings (8 at most), which
+    cosh multiplies by its size: 8 * 711 * 1.2e-16 of a cell's largest value."""
+    p, v, sigma, chi = state(32, 0.0)
+    sigma[4] = np.linspace(709.8, 710.4, sigma[4].size).reshape(sigma[4].shape) / p["beta"]
+    sigma[[0, 1, 2, 3, 5]] = 0.0
+    p = dict(p, n_sub=n_sub, beta=sign * p["beta"])
+    # a step in which the plastic terms are of the order of the stress (the rate
+    # is about 1e296), but for the implicit form, which takes any
+    dt = 1e-297 if n_sub == 1 else 10.0
+    ss, c1, rs, rc = step(p, dt, v, sigma, chi)
+    assert np.isfinite(rs).all() and np.isfinite(rc).all()
+    assert np.abs(rs - sigma).max() > 1e-3
+    assert np.abs(ss - rs).max() <= 7e-13 * np.abs(rs).max()
+    assert np.abs(c1 - rc).max() <= 7e-13 * np.abs(rc).max()
+
+
+@pytest.mark.parametrize("n_sub", [1, 4, -1, -2])
+def test_negative_beta(n_sub):
+    """cosh is even: a negative beta at ordinary stresses, to the usual bars."""
+    p, v, sigma, chi = state(33, 1.1)
+    p = dict(p, n_sub=n_sub, beta=-p["beta"])
+    ss, c1, rs, rc = step(p, 10.0, v, sigma, chi)
+    assert np.abs(ss - rs).max() <= 1e-12 * np.abs(rs).max()
+    assert np.abs(c1 - rc).max() <= 1e-11 * np.abs(rc - chi).max() + 1e-16
+
+
+def test_negative_beta_far_from_zero():
+    """Sub-steps at beta sbar about -420, where exp(-2 b) alone overflows; bars as
+    for the largest arguments."""
+    p, v, sigma, chi = state(34, 0.0)
+    sigma[4] = np.linspace(415.0, 420.0, sigma[4].size).reshape(sigma[4].shape) / p["beta"]
+    sigma[[0, 1, 2, 3, 5]] = 0.0
+    chi[:] = 0.04
+    D = ostz.plastic_rate(sigma[4].max(), 0.04, p)
+    p = dict(p, n_sub=4, beta=-p["beta"])
+    # the fastest cell loses 1e-4 of its stress (0.04 of the argument's unit)
+    dt = 1e-4 * sigma[4].max() / (2 * MU * D)
+    ss, c1, rs, rc = step(p, dt, v, sigma, chi)
+    assert np.abs(rs - sigma).max() > 1e-5
+    assert np.abs(ss - rs).max() <= 7e-13 * np.abs(rs).max()
+    assert np.abs(c1 - rc).max() <= 7e-13 * np.abs(rc).max()
