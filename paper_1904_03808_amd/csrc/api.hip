@@ -146,12 +146,6 @@ void carve(const qs_params* p, const std::vector<int>& dims, char* base, qs_hand
         lb.r32 = cv.take<float>(e);
         lb.y32 = cv.take<float>(e);
       }
-      // the setup of the bottom map runs its cycle in FP64
-      if (bl >= 1 && l >= bl) {
-        lb.x64 = cv.take<double>(e);
-        lb.b64 = cv.take<double>(e);
-        lb.r64 = cv.take<double>(e);
-      }
     }
     const size_t planes = static_cast<size_t>(lb.d.nz + 1);
     lb.S64 = cv.take<double>(planes * kStencil);
@@ -464,18 +458,6 @@ void vcycle(qs_handle* hd, int l, T* x, const T* b, bool x_zero = false, bool be
   smooth<T>(hd, l, x, b, hd->p.n_post, true);
 }
 
-// Blocks of the bottom map: the FP64 cycle of the two coarsest levels on every
-// unit right-hand side, each response transformed into one column per mode.
-void build_bottom(qs_handle* hd) {
-  const int l = hd->nlev - 2;
-  LevelBufs& lb = hd->L[l];
-  for (int u = 0; u < bottom_unknowns(lb.d); ++u) {
-    launch_bottom_unit(lb.b64, lb.x64, lb.d, u, hd->stream);
-    vcycle<double>(hd, l, lb.x64, lb.b64);
-    launch_bottom_column(lb.x64, lb.d, hd->bottom_tw, u, hd->bottom_M, hd->stream);
-  }
-}
-
 // ||b - K x||^2 on level 0 in FP64 (optionally writing the residual, scaled,
 // in FP32 for the refinement loop); result in hd->dnorm[0].
 template <typename Tout>
@@ -701,7 +683,9 @@ qs_status qs_setup(const qs_params* p, void* workspace, size_t workspace_bytes, 
                                         hipMemcpyHostToDevice, hd->stream);
     if (e != hipSuccess) st = hip_fail("hipMemcpyAsync (roots of unity)", e);
     if (st == QS_OK) {
-      build_bottom(hd);
+      const LevelBufs& lb = hd->L[hd->nlev - 2];
+      launch_bottom_build(lb.S64, lb.D64, hd->Ainv, hd->ncoarse, lb.d, hd->bottom_tw, p->colour_order,
+                          p->n_pre, p->n_post, hd->bottom_M, hd->stream);
       st = launch_check();
       hd->bottom = st == QS_OK;
     }

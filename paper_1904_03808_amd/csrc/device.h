@@ -165,11 +165,14 @@ void launch_coarse_solve(const double* Ainv, int n, const T* b, T* x, Dims d, hi
 // exp(2 pi i s / cx), then exp(2 pi i s / cy) (real and imaginary parts; cx, cy
 // the coarsest sizes).
 bool bottom_supported(Dims d);
-int bottom_unknowns(Dims d);  // per block; also the unit right-hand sides of the setup
+int bottom_unknowns(Dims d);  // per block
 size_t bottom_matrix_values(Dims d);
 size_t bottom_vector_values(Dims d);
-void launch_bottom_unit(double* b, double* x, Dims d, int u, hipStream_t s);
-void launch_bottom_column(const double* x, Dims d, const double* tw, int u, double* M, hipStream_t s);
+// All blocks, from the level's stencil and inverse centre blocks, the coarsest
+// inverse (ncoarse unknowns), the colour order and the sweeps of a cycle.
+void launch_bottom_build(const double* S, const double* Dinv, const double* Ainv, int ncoarse, Dims d,
+                         const double* tw, const int order[8], int n_pre, int n_post, double* M,
+                         hipStream_t s);
 // x = (V-cycle of level d and the coarsest, from zero) b, walls not written
 template <typename T>
 void launch_bottom(const double* M, const double* tw, const T* b, T* x, double* yh, Dims d,

@@ -7,10 +7,9 @@
 // so the map commutes with shifts by two columns or rows: Fourier modes over
 // the cx * cy shifts (cx, cy the coarsest sizes) split it into independent
 // blocks of n = 12 (nz - 1) unknowns (component, plane, y parity, x parity).
-// The blocks are computed at setup by running that cycle in FP64 on the n unit
-// right-hand sides (bottom_column), for whatever sweeps and colour order the
-// handle has, and are held and applied in FP64 in both precisions, as the
-// coarsest inverse is.
+// The blocks are computed at setup in FP64 (k_bottom_build), for whatever sweeps
+// and colour order the handle has, and are held and applied in FP64 in both
+// precisions, as the coarsest inverse is.
 //
 // The map commutes with the reflections in x and y as well, which keep every
 // node's colour.  Taken about the nodes' own positions (half a shift for the odd
@@ -34,6 +33,7 @@ constexpr int kThreads = 512;              // of the kernels that transform b
 constexpr int kRows = 32;                  // rows of a block per workgroup
 constexpr int kGroups = kThreads / kRows;  // column groups per workgroup
 constexpr int kBatch = 8;                  // loads in flight per thread in the transform
+constexpr size_t kMaxLds = 64ull << 10;    // bytes a workgroup may take
 
 // Modes (mx, my) kept: one of each conjugate pair.  mx = 0 and 2 mx = cx pair
 // (mx, my) with (mx, -my), the other mx with cx - mx.
@@ -235,32 +235,133 @@ __global__ __launch_bounds__(256) void k_bottom_back(const double2* __restrict__
   }
 }
 
-// Unit right-hand side of unknown u at shift 0: b = 0 but for one node.
-__global__ __launch_bounds__(256) void k_bottom_unit(double* __restrict__ b, double* __restrict__ x,
-                                                     int total, int at) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= total) return;
-  b[t] = t == at ? 1.0 : 0.0;
-  x[t] = 0.0;
+// A stencil entry between components c and d, at the phase a between the two
+// nodes, as it enters the real blocks (f_c conj(f_d) exp(i a), f = 1, 1, i, whose
+// imaginary part cancels against the mirrored entry's).
+__device__ __forceinline__ double real_phase(int c, int d, double sn, double cs) {
+  return (c == 2) == (d == 2) ? cs : (c == 2 ? -sn : sn);
 }
 
-// Column u of every block from the response x to unit u.
-__global__ __launch_bounds__(kThreads) void k_bottom_column(const double* __restrict__ x, int nx, int ny,
-                                                       int nz, const double2* __restrict__ tw, int u,
-                                                       double* __restrict__ M) {
+// The map's blocks, one column per wavefront.  In the real basis the level's
+// operator couples plane k to k - 1, k, k + 1 and each (y, x) parity to the same
+// or the other one by 108 numbers a plane (G, the stencil summed over its mirrored
+// entries at the mode's phases), the transfers are products of cosines, and the
+// coarsest inverse is a matrix B of 3 (nzc - 1) unknowns: a column is the cycle run
+// on one unit vector of 12 (nz - 1) values in LDS.  Everything is a fixed cost of
+// about forty short phases, and all columns of all blocks are one launch.  Running
+// the level kernels on every unit right-hand side instead took 20 launches each:
+// setup of 16^3 (map of 8^3 over 4^3, 84 unknowns) 6.9 -> 0.74 ms, of 96^3 36.3 ->
+// 25.5 ms, of 256^3 474 -> 457 ms, the rest of it on the host.
+__global__ __launch_bounds__(256) void k_bottom_build(const double* __restrict__ S,
+                                                      const double* __restrict__ Dinv,
+                                                      const double* __restrict__ Ainv, int ncoarse, int nx,
+                                                      int ny, int nz, const double2* __restrict__ tw,
+                                                      unsigned order, int n_pre, int n_post,
+                                                      double* __restrict__ M) {
   extern __shared__ __align__(16) unsigned char smem[];
-  const int cx = nx / 2, cy = ny / 2, n = 12 * (nz - 1);
-  double2* ltw = reinterpret_cast<double2*>(smem);
-  double2* xh = ltw + cx + cy;
-  double2* part = xh + n;
-  int mx, my;
-  mode_of(blockIdx.x, cx, cy, &mx, &my);
-  if (2 * my > cy) return;  // the block of (mx, cy - my) serves
-  load_twiddles(tw, cx, cy, ltw);
-  forward_mode<double>(x, nx, ny, nz, mx, my, ltw, ltw + cx, part, xh);
-  double* col = M + (static_cast<size_t>(block_of(mx, my, cx, cy)) * n + u) * n;
-  const double2 w = real_factor(u, nz, mx, my, cx, cy);
-  for (int t = threadIdx.x; t < n; t += blockDim.x) col[t] = xh[t].x * w.x + xh[t].y * w.y;
+  const int cx = nx / 2, cy = ny / 2, Z = nz - 1, ZC = nz / 2 - 1, n = 12 * Z, m = 3 * ZC;
+  const int mx = blockIdx.x % (cx / 2 + 1), my = blockIdx.x / (cx / 2 + 1);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+  double* G = reinterpret_cast<double*>(smem);  // [plane][oz][parity change][c][d]
+  double* B = G + 108 * Z;                      // [c, K][d, K']
+  double* y = B + m * m + 2 * n * wave;         // this wavefront's column
+  double* r = y + n;                            // its residual, then the coarse vectors
+  double sx, cosx, sy, cosy;                    // of the phase of one column, one row
+  sincospi(static_cast<double>(mx) / cx, &sx, &cosx);
+  sincospi(static_cast<double>(my) / cy, &sy, &cosy);
+  for (int e = threadIdx.x; e < 108 * Z; e += blockDim.x) {
+    const int d = e % 3, c = e / 3 % 3, par = e / 9 % 4, oz = e / 36 % 3, k = 1 + e / 108;
+    const int px = par & 1, py = par >> 1;
+    double g = 0.0;
+    for (int oy = -py; oy <= py; oy += 2)
+      for (int ox = -px; ox <= px; ox += 2) {
+        const double c1 = ox ? cosx : 1.0, s1 = ox * sx, c2 = oy ? cosy : 1.0, s2 = oy * sy;
+        g += S[(k * 27 + oz * 9 + (oy + 1) * 3 + ox + 1) * 9 + c * 3 + d] *
+             real_phase(c, d, s1 * c2 + c1 * s2, c1 * c2 - s1 * s2);
+      }
+    G[e] = g;
+  }
+  for (int e = threadIdx.x; e < m * m; e += blockDim.x) {
+    const int q = e % m, row = e / m;
+    const double* a = Ainv + static_cast<size_t>(row) * cx * cy * ncoarse + q * cx * cy;
+    double g = 0.0;
+    for (int J = 0; J < cy; ++J) {
+      const double2 wy = tw[cx + my * J % cy];
+      for (int I = 0; I < cx; ++I) {
+        const double2 wx = tw[mx * I % cx];
+        g += a[J * cx + I] * real_phase(row / ZC, q / ZC, wx.y * wy.x + wx.x * wy.y,
+                                        wx.x * wy.x - wx.y * wy.y);
+      }
+    }
+    B[e] = g;
+  }
+  const int u = blockIdx.y * waves + wave;  // a wavefront past the last column runs along
+  for (int t = lane; t < n; t += 64) y[t] = 0.0;
+  __syncthreads();
+  // sum of the operator's row (c, k, par) times y, with or without the node itself
+  auto row_sum = [&](int c, int k, int par, bool own) {
+    double s = 0.0;
+    for (int oz = 0; oz < 3; ++oz) {
+      const int kk = k + oz - 1;
+      if (kk < 1 || kk > Z) continue;
+      const double* g = G + ((k - 1) * 3 + oz) * 36 + c * 3;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        if (oz == 1 && q == 0 && !own) continue;
+#pragma unroll
+        for (int d = 0; d < 3; ++d) s += g[q * 9 + d] * y[(d * Z + kk - 1) * 4 + (par ^ q)];
+      }
+    }
+    return s;
+  };
+  auto smooth = [&](int sweeps, bool reverse) {
+    for (int q = 0; q < 8 * sweeps; ++q) {
+      const int col = order >> (4 * (reverse ? 7 - q % 8 : q % 8)) & 7;
+      const int par = col & 3, first = col & 4 ? 1 : 2;
+      // lane: a component and plane of the colour (at most 48)
+      const int c = lane % 3, k = first + 2 * (lane / 3);
+      const int t = (c * Z + k - 1) * 4 + par;
+      double v = 0.0;
+      if (k <= Z) v = Dinv[k * 9 + c * 4] * ((t == u ? 1.0 : 0.0) - row_sum(c, k, par, false));
+      if (k <= Z) y[t] = v;  // nodes of one colour do not couple
+      __syncthreads();
+    }
+  };
+  smooth(n_pre, false);
+  for (int t = lane; t < n; t += 64)
+    r[t] = (t == u ? 1.0 : 0.0) - row_sum(t / (4 * Z), 1 + t / 4 % Z, t & 3, true);
+  __syncthreads();
+  const int c = lane / ZC, K = 1 + lane % ZC;  // coarse unknown of this lane (m <= 45)
+  double v = 0.0;
+  if (lane < m)
+    for (int dz = -1; dz <= 1; ++dz) {
+      const double* p = r + (c * Z + 2 * K + dz - 1) * 4;
+      v += (dz ? 0.5 : 1.0) * (p[0] + cosx * p[1] + cosy * (p[2] + cosx * p[3]));
+    }
+  __syncthreads();
+  if (lane < m) r[lane] = v;
+  __syncthreads();
+  v = 0.0;
+  if (lane < m)
+    for (int q = 0; q < m; ++q) v += B[lane * m + q] * r[q];
+  __syncthreads();
+  if (lane < m) r[lane] = v;
+  __syncthreads();
+  for (int t = lane; t < n; t += 64) {
+    const int ct = t / (4 * Z), k = 1 + t / 4 % Z, K0 = k >> 1, K1 = (k + 1) >> 1;
+    const double lo = K0 >= 1 ? r[ct * ZC + K0 - 1] : 0.0, hi = K1 <= ZC ? r[ct * ZC + K1 - 1] : 0.0;
+    y[t] += 0.5 * (lo + hi) * (t & 1 ? cosx : 1.0) * (t & 2 ? cosy : 1.0);
+  }
+  __syncthreads();
+  smooth(n_post, true);
+  if (u >= n) return;
+  double* col = M + (static_cast<size_t>(blockIdx.x) * n + u) * n;
+  for (int t = lane; t < n; t += 64) col[t] = y[t];
+}
+
+size_t build_lds(Dims d, int waves) {
+  const size_t Z = d.nz - 1, m = 3 * (d.nz / 2 - 1);
+  return (108 * Z + m * m + 24 * Z * waves) * sizeof(double);
 }
 
 size_t modes_lds(Dims d) {
@@ -291,22 +392,24 @@ size_t bottom_vector_values(Dims d) {
 // which the coarsest inverse streams.  The block size also bounds the setup
 // (one cycle per unknown).  The transforms stage their sums in LDS (64 KB).
 bool bottom_supported(Dims d) {
-  constexpr size_t kMaxBytes = 48ull << 20, kMaxLds = 64ull << 10;
+  constexpr size_t kMaxBytes = 48ull << 20;
   const size_t n = static_cast<size_t>(bottom_unknowns(d));
   return n <= 384 && n * n * mode_count(d.nx / 2, d.ny / 2) * sizeof(double) <= kMaxBytes &&
          modes_lds(d) <= kMaxLds && back_lds(d) <= kMaxLds;
 }
 
-void launch_bottom_unit(double* b, double* x, Dims d, int u, hipStream_t s) {
-  const int ex = u & 1, ey = (u >> 1) & 1, q = u >> 2, c = q / (d.nz - 1), k = 1 + q % (d.nz - 1);
-  const int total = static_cast<int>(d.elems());
-  const int at = c * d.comp() + k * d.plane() + ey * d.nx + ex;
-  hipLaunchKernelGGL(k_bottom_unit, dim3((total + 255) / 256), dim3(256), 0, s, b, x, total, at);
-}
-
-void launch_bottom_column(const double* x, Dims d, const double* tw, int u, double* M, hipStream_t s) {
-  hipLaunchKernelGGL(k_bottom_column, dim3(mode_count(d.nx / 2, d.ny / 2)), dim3(kThreads), modes_lds(d), s,
-                     x, d.nx, d.ny, d.nz, reinterpret_cast<const double2*>(tw), u, M);
+void launch_bottom_build(const double* S, const double* Dinv, const double* Ainv, int ncoarse, Dims d,
+                         const double* tw, const int order[8], int n_pre, int n_post, double* M,
+                         hipStream_t s) {
+  unsigned packed = 0;
+  for (int q = 0; q < 8; ++q) packed |= static_cast<unsigned>(order[q]) << (4 * q);
+  // four columns per workgroup, fewer where 64 KB do not hold them (the deepest levels)
+  int waves = 4;
+  while (waves > 1 && build_lds(d, waves) > kMaxLds) --waves;
+  const int n = bottom_unknowns(d);
+  hipLaunchKernelGGL(k_bottom_build, dim3(block_count(d.nx / 2, d.ny / 2), (n + waves - 1) / waves),
+                     dim3(64 * waves), build_lds(d, waves), s, S, Dinv, Ainv, ncoarse, d.nx, d.ny, d.nz,
+                     reinterpret_cast<const double2*>(tw), packed, n_pre, n_post, M);
 }
 
 template <typename T>
