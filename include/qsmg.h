@@ -32,11 +32,16 @@
  * the library.
  *
  * Streams.  All work is enqueued on the stream given to qs_setup() (a
- * hipStream_t passed as void*; NULL = default stream).  Entry points that
- * return host-visible results (qs_mg_solve, qs_projection_step) wait once
- * per V-cycle (the calling thread polls) for the residual norm and return when
- * the last one is there and the stream idle (but for an FP32-IR solve's copy of
- * the iterate into x); the others are asynchronous.  Calls on one handle must not overlap.
+ * hipStream_t passed as void*; NULL = default stream), and outputs are complete
+ * in the order of that stream: work enqueued on it later sees them, another
+ * stream or the host has to wait for it first.  qs_setup() waits for its own
+ * work.  Entry points that return host-visible results (qs_mg_solve and the
+ * projection steps) wait for the residual norm once per V-cycle (the calling
+ * thread polls), so the cycles of the solve are done when they return; what
+ * follows them may still run: the clearing of x for a zero right-hand side, an
+ * FP32-IR solve's copy of the iterate into x, a step's stress correction and the
+ * copy of chi.  The others are asynchronous.  Calls on one handle must not
+ * overlap.
  *
  * Errors.  Every entry point returns a qs_status; nothing is thrown and the
  * process is never aborted.  On QS_ERR_HIP the stream may hold partial work.
