@@ -314,6 +314,10 @@ qs_status qs_coarse_solve(qs_handle* hd, double* x, const double* b);
  * Used to time the smoother on its own and to test it. */
 qs_status qs_smooth(qs_handle* hd, int level, void* x, const void* b, int sweeps);
 
+/* Test-facing: with rows = 1 the fine level of this handle is swept by the row
+ * kernel also where its size asks for tiles; 0 (as after qs_setup): by size. */
+qs_status qs_fine_sweep_rows(qs_handle* hd, int rows);
+
 /* Copy the FP64 per-plane stencil of level `level` to host memory:
  * out[(nz+1)][27][3][3], offset index (oz+1)*9 + (oy+1)*3 + (ox+1). */
 qs_status qs_level_stencil(qs_handle* hd, int level, double* out_host);

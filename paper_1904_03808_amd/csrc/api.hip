@@ -107,6 +107,7 @@ struct qs_handle {
   double* pinned_dev = nullptr;  // the same memory as the device addresses it (null: copy instead)
   double ticket = 0.0;       // of the last norm asked for
   bool row_sweep = false;    // colour order allows the row-parity sweep kernel
+  bool rows_only = false;    // tests: no tile sweep (qs_fine_sweep_rows)
   size_t lds_limit = 0;      // bytes of LDS a workgroup may use
   void* static_scratch = nullptr;  // device address of `scratch` on this handle's device (or null)
 };
@@ -329,6 +330,13 @@ bool use_row_sweep(qs_handle* hd, int l) {
   return l == 0 && hd->row_sweep && sweep_supported(hd->L[l].d, hd->lds_limit, sizeof(T));
 }
 
+// Rows per tile where the fine level is swept by tiles (sweep_tile_rows), 0 where
+// by rows.
+template <typename T>
+int tile_rows(const qs_handle* hd, Dims d, int* halves) {
+  return hd->rows_only ? 0 : sweep_tile_rows(d, hd->lds_limit, sizeof(T), halves);
+}
+
 // One sweep of the fine level by tiles, from src into dst.
 template <typename T>
 void tile_sweep(qs_handle* hd, LevelBufs& lb, const T* src, T* dst, const T* b, int tr, int halves,
@@ -353,7 +361,7 @@ bool begin_smooth(qs_handle* hd, const double* x, const double* b) {
   int halves = 0;
   if (!hd->pinned_dev || hd->nlev < (hd->bottom ? 3 : 2) || hd->p.n_pre < 1 || !use_row_sweep<double>(hd, 0))
     return false;
-  const int tr = sweep_tile_rows(lb.d, hd->lds_limit, sizeof(double), &halves);
+  const int tr = tile_rows<double>(hd, lb.d, &halves);
   if (tr <= 0) return false;
   tile_sweep<double>(hd, lb, x, lb.y64, b, tr, halves, false, false);
   return true;
@@ -399,7 +407,7 @@ void smooth(qs_handle* hd, int l, T* x, const T* b, int sweeps, bool reverse,
   T* oth = y;
   const int rp0 = reverse ? 1 : 0, pf = reverse ? 1 : 0, xf = reverse ? 1 : 0;
   int halves = 0;
-  const int tr = sweep_tile_rows(lb.d, hd->lds_limit, sizeof(T), &halves);
+  const int tr = tile_rows<T>(hd, lb.d, &halves);
   if (begun) std::swap(cur, oth);
   for (int s = begun ? 1 : 0; s < sweeps; ++s) {
     const bool z = x_zero && s == 0 && !reverse;
@@ -448,8 +456,7 @@ void vcycle(qs_handle* hd, int l, T* x, const T* b, bool x_zero = false, bool be
   }
   vcycle<T>(hd, l + 1, Prec<T>::x(cb), Prec<T>::b(cb));
   int halves = 0;
-  if (hd->p.n_post >= 1 && use_row_sweep<T>(hd, l) &&
-      !sweep_tile_rows(lb.d, hd->lds_limit, sizeof(T), &halves)) {
+  if (hd->p.n_post >= 1 && use_row_sweep<T>(hd, l) && !tile_rows<T>(hd, lb.d, &halves)) {
     // the first post-smoothing sweep applies the prolongated correction
     smooth<T>(hd, l, x, b, hd->p.n_post, true, false, Prec<T>::x(cb));
     return;
@@ -1122,6 +1129,12 @@ qs_status qs_smooth(qs_handle* hd, int level, void* x, const void* b, int sweeps
     if (lb.y64 && level > 0) zero_walls<double>(lb.y64, lb.d, hd->stream);
   }
   return launch_check();
+}
+
+qs_status qs_fine_sweep_rows(qs_handle* hd, int rows) {
+  if (!hd || (rows != 0 && rows != 1)) return QS_ERR_ARG;
+  hd->rows_only = rows == 1;
+  return QS_OK;
 }
 
 qs_status qs_level_stencil(qs_handle* hd, int level, double* out_host) {

@@ -304,6 +304,9 @@ class MGSolver:
                 raise ValueError("%s must be a contiguous %s CUDA tensor of shape %s" % (name, dt, s))
         check(self._lib.qs_smooth(self._h, level, _ptr(x), _ptr(b), int(sweeps)), "qs_smooth")
 
+    def fine_sweep_rows(self, rows: bool):
+        check(self._lib.qs_fine_sweep_rows(self._h, int(rows)), "qs_fine_sweep_rows")
+
     def level_stencil(self, level: int):
         import numpy as np
         nx, ny, nz = self.level_dims(level)
