@@ -314,6 +314,12 @@ qs_status qs_coarse_solve(qs_handle* hd, double* x, const double* b);
  * Used to time the smoother on its own and to test it. */
 qs_status qs_smooth(qs_handle* hd, int level, void* x, const void* b, int sweeps);
 
+/* Test-facing: b_coarse = T^T (b - A x) (level -> level+1) as the V-cycle forms
+ * it, in the handle's working precision (see qs_smooth; x and b 16-byte
+ * aligned).  Writes the interior of b_coarse. */
+qs_status qs_level_residual_restrict(qs_handle* hd, int level, const void* x, const void* b,
+                                     void* b_coarse);
+
 /* Test-facing: with rows = 1 the fine level of this handle is swept by the row
  * kernel also where its size asks for tiles; 0 (as after qs_setup): by size. */
 qs_status qs_fine_sweep_rows(qs_handle* hd, int rows);

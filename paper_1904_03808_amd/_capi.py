@@ -83,6 +83,7 @@ SIGNATURES = {
     "qs_coarse_solve": [_P, _P, _P],
     "qs_level_stencil": [_P, _I, _P],
     "qs_smooth": [_P, _I, _P, _P, _I],
+    "qs_level_residual_restrict": [_P, _I, _P, _P, _P],
     "qs_fine_sweep_rows": [_P, _I],
 }
 

@@ -430,6 +430,19 @@ void smooth(qs_handle* hd, int l, T* x, const T* b, int sweeps, bool reverse,
     (void)hipMemcpyAsync(x, cur, lb.d.elems() * sizeof(T), hipMemcpyDeviceToDevice, hd->stream);
 }
 
+// bc = T^T (b - A x), and xc = 0 (if given), on the interior of level l + 1
+template <typename T>
+void residual_restrict(qs_handle* hd, int l, const T* x, const T* b, T* bc, T* xc) {
+  LevelBufs& lb = hd->L[l];
+  if (l == 0) {
+    launch_resid_restrict<T>(x, b, bc, xc, lb.d, hd->fc64, hd->stream);
+    return;
+  }
+  T* r = Prec<T>::r(lb);
+  residual<T>(hd, l, x, b, r, false);
+  launch_restrict<T>(r, bc, xc, lb.d, hd->stream);
+}
+
 // x_zero: x is zero on entry and need not hold it (see smooth; only when the
 // row sweep smooths level l and n_pre >= 1); begun: see smooth
 template <typename T>
@@ -447,13 +460,7 @@ void vcycle(qs_handle* hd, int l, T* x, const T* b, bool x_zero = false, bool be
   LevelBufs& cb = hd->L[l + 1];
   // the restriction also clears the interior of the coarse correction (its
   // walls are zero from setup and never written)
-  if (l == 0) {
-    launch_resid_restrict<T>(x, b, Prec<T>::b(cb), Prec<T>::x(cb), lb.d, hd->fc64, hd->stream);
-  } else {
-    T* r = Prec<T>::r(lb);
-    residual<T>(hd, l, x, b, r, false);
-    launch_restrict<T>(r, Prec<T>::b(cb), Prec<T>::x(cb), lb.d, hd->stream);
-  }
+  residual_restrict<T>(hd, l, x, b, Prec<T>::b(cb), Prec<T>::x(cb));
   vcycle<T>(hd, l + 1, Prec<T>::x(cb), Prec<T>::b(cb));
   int halves = 0;
   if (hd->p.n_post >= 1 && use_row_sweep<T>(hd, l) && !tile_rows<T>(hd, lb.d, &halves)) {
@@ -1128,6 +1135,20 @@ qs_status qs_smooth(qs_handle* hd, int level, void* x, const void* b, int sweeps
     smooth<double>(hd, level, xd, static_cast<const double*>(b), sweeps, false);
     if (lb.y64 && level > 0) zero_walls<double>(lb.y64, lb.d, hd->stream);
   }
+  return launch_check();
+}
+
+qs_status qs_level_residual_restrict(qs_handle* hd, int level, const void* x, const void* b,
+                                     void* b_coarse) {
+  if (!hd || level < 0 || level >= hd->nlev - 1 || !x || !b || !b_coarse || !aligned16(x) ||
+      !aligned16(b))
+    return QS_ERR_ARG;
+  if (hd->p.precision == QS_FP32_IR)
+    residual_restrict<float>(hd, level, static_cast<const float*>(x), static_cast<const float*>(b),
+                             static_cast<float*>(b_coarse), nullptr);
+  else
+    residual_restrict<double>(hd, level, static_cast<const double*>(x), static_cast<const double*>(b),
+                              static_cast<double*>(b_coarse), nullptr);
   return launch_check();
 }
 

@@ -296,12 +296,22 @@ class MGSolver:
         check(self._lib.qs_coarse_solve(self._h, self._chk(x, s, "x"), self._chk(b, s, "b")),
               "qs_coarse_solve")
 
-    def smooth(self, level: int, x, b, sweeps: int):
+    def _chk_working(self, level: int, x, b):
         s = self.node_shape(level)
         dt = torch.float32 if self.precision == "fp32-ir" else torch.float64
         for t, name in ((x, "x"), (b, "b")):
             if t.dtype != dt or tuple(t.shape) != s or not t.is_contiguous() or t.device.type != "cuda":
                 raise ValueError("%s must be a contiguous %s CUDA tensor of shape %s" % (name, dt, s))
+
+    def level_residual_restrict(self, level: int, x, b):
+        self._chk_working(level, x, b)
+        bc = torch.zeros(self.node_shape(level + 1), dtype=x.dtype, device=self.device)
+        check(self._lib.qs_level_residual_restrict(self._h, level, _ptr(x), _ptr(b), _ptr(bc)),
+              "qs_level_residual_restrict")
+        return bc
+
+    def smooth(self, level: int, x, b, sweeps: int):
+        self._chk_working(level, x, b)
         check(self._lib.qs_smooth(self._h, level, _ptr(x), _ptr(b), int(sweeps)), "qs_smooth")
 
     def fine_sweep_rows(self, rows: bool):
