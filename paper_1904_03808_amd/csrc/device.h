@@ -73,7 +73,7 @@ void launch_residual_pair_gen(const T* x, const T* b, T* r, Dims d, const T* Pst
 // Fine-level row-parity half sweep (kernels_sweep.hip): updates every node
 // of the rows with parity row_par, reading own rows from own_src, neighbour
 // rows from nbr_src and writing dst.  zero = 1: own rows are known to be 0
-// and not read; zero = 2: own and neighbour rows (x_first = 0 only).
+// and not read; zero = 2: own and neighbour rows (both x_first = 0, FP32 only).
 // zero = 3: own and neighbour rows are read as x + T ec (the coarse
 // correction ec prolongated on the fly); zero = 4: own rows only (both
 // x_first = 1, row_par 1 and 0, the two halves of the first post-smoothing
@@ -92,7 +92,7 @@ void sweep_set_lds_limit(size_t bytes);
 // row_first first, planes and columns of parity 0 first (reverse: 1); nbr is
 // src.  halves = 1: the rows of parity row_first alone, from src, with the rows
 // between them from nbr.  zero = 1 (halves = 1): the updated rows are known to
-// be 0 and not read; 2: all rows.  tr (rows a workgroup owns) and halves come
+// be 0 and not read; 2: all rows (both FP32 only).  tr (rows a workgroup owns) and halves come
 // from sweep_tile_rows (0: the tile sweep is not used).
 int sweep_tile_rows(Dims d, size_t lds_limit, int bytes_per_value, int* halves);
 template <typename T>

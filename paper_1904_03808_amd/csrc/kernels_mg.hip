@@ -968,11 +968,10 @@ bool pair_rows_in_lanes(Dims d) {
   return d.nx % 2 == 0 && W >= 1 && W <= 64 && (W & (W - 1)) == 0;
 }
 
-// How the pair kernels get the outer columns of a row (window3).
+// How the pair kernels get the outer columns of a row whose pairs do not fill a
+// run of lanes (window3).
 template <typename T>
-int pair_shuffle(Dims d) {
-  return pair_rows_in_lanes(d) ? 1 : (sizeof(T) == 4 ? 2 : 0);
-}
+constexpr int kPairShuffle = sizeof(T) == 4 ? 2 : 0;
 
 bool colour_pair_supported(Dims d) { return d.nx % 2 == 0 && d.nx >= 2 && d.nx <= 512; }
 
@@ -987,15 +986,13 @@ void launch_colour_pair_gen(T* x, const T* b, Dims d, int colour, const T* Pst, 
   // at 128^3)
   const int rpb = std::max(1, std::min(cr.hy, 128 / W));
   const dim3 grid(blocks_for(cr.hy, rpb), cr.nk);
-  // outer window columns: see window3
-  const int sh = pair_shuffle<T>(d);
-#define QS_PAIR1(KERNEL, XF, G, B, ...)                                                             \
-  if (sh == 1)                                                                                      \
+  const bool lanes = pair_rows_in_lanes(d);
+#define QS_PAIR1(KERNEL, XF, G, B, ...)                                                              \
+  if (lanes)                                                                                         \
     hipLaunchKernelGGL((KERNEL<T, XF, 1>), G, B, 0, s, x, b, d.nx, d.ny, d.nz, cr, rpb, __VA_ARGS__); \
-  else if (sh == 2)                                                                                 \
-    hipLaunchKernelGGL((KERNEL<T, XF, 2>), G, B, 0, s, x, b, d.nx, d.ny, d.nz, cr, rpb, __VA_ARGS__); \
-  else                                                                                              \
-    hipLaunchKernelGGL((KERNEL<T, XF, 0>), G, B, 0, s, x, b, d.nx, d.ny, d.nz, cr, rpb, __VA_ARGS__);
+  else                                                                                               \
+    hipLaunchKernelGGL((KERNEL<T, XF, kPairShuffle<T>>), G, B, 0, s, x, b, d.nx, d.ny, d.nz, cr, rpb, \
+                       __VA_ARGS__);
 #define QS_PAIR(KERNEL, G, B, ...)         \
   if (cr.a) {                              \
     QS_PAIR1(KERNEL, 1, G, B, __VA_ARGS__) \
@@ -1019,13 +1016,11 @@ template <typename T>
 void launch_residual_pair_gen(const T* x, const T* b, T* r, Dims d, const T* Pst, hipStream_t s) {
   const dim3 grid(blocks_for(static_cast<long long>(d.nx / 2) * d.ny, 256), d.nz - 1);
   if (d.nz - 1 <= 0) return;
-  const int sh = pair_shuffle<T>(d);
-  if (sh == 1)
+  if (pair_rows_in_lanes(d))
     hipLaunchKernelGGL((k_residual_pair_gen<T, 1>), grid, dim3(256), 0, s, x, b, r, d.nx, d.ny, d.nz, Pst);
-  else if (sh == 2)
-    hipLaunchKernelGGL((k_residual_pair_gen<T, 2>), grid, dim3(256), 0, s, x, b, r, d.nx, d.ny, d.nz, Pst);
   else
-    hipLaunchKernelGGL((k_residual_pair_gen<T, 0>), grid, dim3(256), 0, s, x, b, r, d.nx, d.ny, d.nz, Pst);
+    hipLaunchKernelGGL((k_residual_pair_gen<T, kPairShuffle<T>>), grid, dim3(256), 0, s, x, b, r, d.nx,
+                       d.ny, d.nz, Pst);
 }
 
 int residual_blocks(Dims d) {

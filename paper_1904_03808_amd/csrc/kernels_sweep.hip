@@ -550,12 +550,12 @@ void launch_stride(const T* own_src, const T* nbr_src, T* dst, const T* b, const
     QS_SWEEP(1, 4);
   else if (a.x_first)
     QS_SWEEP(1, 0);
-  else if (zero == 2)
-    QS_SWEEP(0, 2);
-  else if (zero == 1)
-    QS_SWEEP(0, 1);
-  else
+  else if (zero == 0)
     QS_SWEEP(0, 0);
+  if constexpr (sizeof(T) == 4) {
+    if (zero == 2) QS_SWEEP(0, 2);
+    if (zero == 1) QS_SWEEP(0, 1);
+  }
 #undef QS_SWEEP
 }
 
@@ -569,6 +569,10 @@ void launch_stride(const T* own_src, const T* nbr_src, T* dst, const T* b, const
 #define QS_STRIDES(X)                                                                     \
   X(36) X(52) X(68) X(84) X(100) X(132) X(164) X(196) X(260) X(324) X(388) X(516) X(772)
 
+// Whether there are kernels of that stride: rows of 768 FP64 values are split.
+template <typename T>
+constexpr bool has_stride(int stride) { return sizeof(T) == 4 || stride != 768 + 2 * kPad; }
+
 int row_stride(int nx, int bytes_per_value) {
   if (nx == 768 && bytes_per_value == 8) return kSplitStride;
 #define QS_FIT(N) \
@@ -580,14 +584,18 @@ int row_stride(int nx, int bytes_per_value) {
 
 template <typename T, int S>
 void set_lds_limit_one(int bytes) {
-  const void* k[6] = {reinterpret_cast<const void*>(&k_sweep_rows<T, S, 0, 0>),
-                      reinterpret_cast<const void*>(&k_sweep_rows<T, S, 1, 0>),
-                      reinterpret_cast<const void*>(&k_sweep_rows<T, S, 0, 1>),
-                      reinterpret_cast<const void*>(&k_sweep_rows<T, S, 0, 2>),
-                      reinterpret_cast<const void*>(&k_sweep_rows<T, S, 1, 3>),
-                      reinterpret_cast<const void*>(&k_sweep_rows<T, S, 1, 4>)};
-  for (const void* f : k)
-    (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  auto set = [&](auto* f) {
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(f), hipFuncAttributeMaxDynamicSharedMemorySize,
+                              bytes);
+  };
+  set(&k_sweep_rows<T, S, 0, 0>);
+  set(&k_sweep_rows<T, S, 1, 0>);
+  set(&k_sweep_rows<T, S, 1, 3>);
+  set(&k_sweep_rows<T, S, 1, 4>);
+  if constexpr (sizeof(T) == 4) {
+    set(&k_sweep_rows<T, S, 0, 1>);
+    set(&k_sweep_rows<T, S, 0, 2>);
+  }
 }
 
 }  // namespace
@@ -617,8 +625,10 @@ int blocks_per_cu(Dims d, int threads, size_t lds) {
   int n = 0;
   const void* k = nullptr;
   switch (row_stride(d.nx, sizeof(T))) {
-#define QS_KERNEL(N) \
-  case N: k = reinterpret_cast<const void*>(&k_sweep_rows<T, N, 0, 0>); break;
+#define QS_KERNEL(N)                                                                            \
+  case N:                                                                                       \
+    if constexpr (has_stride<T>(N)) k = reinterpret_cast<const void*>(&k_sweep_rows<T, N, 0, 0>); \
+    break;
     QS_STRIDES(QS_KERNEL)
 #undef QS_KERNEL
     default:
@@ -690,8 +700,11 @@ void launch_sweep_half(const T* own_src, const T* nbr_src, T* dst, const T* b, c
   const int threads = a.rows * threads_per_row(d.nx, sizeof(T));
   const size_t lds = static_cast<size_t>(sweep_lds_bytes(d, sizeof(T)));
   switch (row_stride(d.nx, sizeof(T))) {
-#define QS_LAUNCH(N) \
-  case N: launch_stride<T, N>(own_src, nbr_src, dst, b, ec, a, cf, zero, threads, lds, s); break;
+#define QS_LAUNCH(N)                                                                        \
+  case N:                                                                                   \
+    if constexpr (has_stride<T>(N))                                                         \
+      launch_stride<T, N>(own_src, nbr_src, dst, b, ec, a, cf, zero, threads, lds, s);      \
+    break;
     QS_STRIDES(QS_LAUNCH)
 #undef QS_LAUNCH
     default:
@@ -702,7 +715,8 @@ void launch_sweep_half(const T* own_src, const T* nbr_src, T* dst, const T* b, c
 
 template <typename T>
 void set_lds_limit_all(size_t bytes) {
-#define QS_LIMIT(N) set_lds_limit_one<T, N>(static_cast<int>(bytes));
+#define QS_LIMIT(N) \
+  if constexpr (has_stride<T>(N)) set_lds_limit_one<T, N>(static_cast<int>(bytes));
   QS_STRIDES(QS_LIMIT)
 #undef QS_LIMIT
   if constexpr (sizeof(T) == 8) set_lds_limit_one<T, kSplitStride>(static_cast<int>(bytes));

@@ -265,17 +265,23 @@ size_t tile_lds(int nx, int tr, int H, int bytes) {
 
 #define QS_STRIDES(X) X(36) X(52) X(68) X(84) X(100) X(132) X(164)
 
+// The kernels there are: whole sweeps up to kFullStride, zero starts in FP32 (the
+// corrections of the refinement) alone.
+template <typename T>
+constexpr bool has_tile(int stride, int H, int Z) {
+  return (H == 1 || stride <= kFullStride) && (Z == 0 || sizeof(T) == 4);
+}
+
 template <typename T, int NXP>
 void launch_stride(const T* src, const T* nbr, T* dst, const T* b, const TileArgs& a,
                    const FineCoef<T>& cf, int H, int Z, int threads, size_t lds, hipStream_t s) {
   const dim3 grid(a.ntr * a.ntp), block(threads);
 #define QS_TILE(H_, Z_)                                                                             \
-  if (H == H_ && Z == Z_)                                                                           \
-  hipLaunchKernelGGL((k_sweep_tile<T, NXP, H_, Z_>), grid, block, lds, s, src, nbr, dst, b, a, cf)
-  if constexpr (NXP <= kFullStride) {
-    QS_TILE(2, 0);
-    QS_TILE(2, 2);
-  }
+  if constexpr (has_tile<T>(NXP, H_, Z_))                                                           \
+    if (H == H_ && Z == Z_)                                                                         \
+      hipLaunchKernelGGL((k_sweep_tile<T, NXP, H_, Z_>), grid, block, lds, s, src, nbr, dst, b, a, cf)
+  QS_TILE(2, 0);
+  QS_TILE(2, 2);
   QS_TILE(1, 0);
   QS_TILE(1, 1);
   QS_TILE(1, 2);
@@ -284,16 +290,15 @@ void launch_stride(const T* src, const T* nbr, T* dst, const T* b, const TileArg
 
 template <typename T, int NXP, int H, int Z>
 void tile_limit_one(int bytes) {
-  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_sweep_tile<T, NXP, H, Z>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  if constexpr (has_tile<T>(NXP, H, Z))
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_sweep_tile<T, NXP, H, Z>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
 }
 
 template <typename T, int NXP>
 void tile_limit(int bytes) {
-  if constexpr (NXP <= kFullStride) {
-    tile_limit_one<T, NXP, 2, 0>(bytes);
-    tile_limit_one<T, NXP, 2, 2>(bytes);
-  }
+  tile_limit_one<T, NXP, 2, 0>(bytes);
+  tile_limit_one<T, NXP, 2, 2>(bytes);
   tile_limit_one<T, NXP, 1, 0>(bytes);
   tile_limit_one<T, NXP, 1, 1>(bytes);
   tile_limit_one<T, NXP, 1, 2>(bytes);
