@@ -19,8 +19,8 @@
 //
 // What bounds it: the cycle it stands for is 16 colour-pair launches, residual,
 // restriction, coarsest solve and correction, each a fixed cost of 3 to 7 us
-// and next to no work (8^3 under 16^3: 21 launches, 90 us).  The map costs about
-// what the coarsest inverse's product alone did.
+// and next to no work (8^3 under 16^3: 20 launches, about 75 us).  The map costs
+// about what the coarsest inverse's product alone did.
 #include <hip/hip_runtime.h>
 
 #include "device.h"
@@ -387,10 +387,15 @@ size_t bottom_vector_values(Dims d) {
   return 2ull * bottom_unknowns(d) * mode_count(d.nx / 2, d.ny / 2);
 }
 
-// The blocks pay as long as reading them costs less than the launches they
-// stand for: 22 launches of about 4 us against kMaxBytes at the 4 to 5 TB/s at
-// which the coarsest inverse streams.  The block size also bounds the setup
-// (one cycle per unknown).  The transforms stage their sums in LDS (64 KB).
+// Where the map is used.  The bounds are of space, not of time: the 20 launches it
+// stands for cost 60 to 80 us, in which 4 TB/s read some 300 MB, and the map won
+// wherever it was tried, V-cycle without and with it 115 -> 55 us at 16^3 over
+// 4^3, 124.5 -> 62 at 32^3 over 8^3, 174 -> 93.5 at 36 x 36 x 64 over 9 x 9 x 16
+// (45 MB read a cycle, 28 held).  The transforms stage their sums in 64 KB of LDS
+// (40 x 40 x 64 over 10 x 10 x 16 does not fit and stays at 184 us); 48 MB read a
+// cycle, a block for every mode, bounds what the workspace holds, where reflected
+// modes share theirs; and up to 384 unknowns k_bottom_build has a lane for every
+// coarse unknown and for every component and plane of a colour.
 bool bottom_supported(Dims d) {
   constexpr size_t kMaxBytes = 48ull << 20;
   const size_t n = static_cast<size_t>(bottom_unknowns(d));
