@@ -88,9 +88,6 @@ constexpr int kHalo = 4;
 constexpr int kSplitW = 384;
 constexpr int kSplitStride = kSplitW + 2 * kHalo + 2 * kPad;
 
-// rows of one parity per workgroup: two at 256 columns, more for shorter rows
-// (at most 256 threads), one at 384, 512 and 768 (384 threads)
-
 // Per-thread state of the sweep, passed by value so that it stays in registers.
 template <typename T, int S>
 struct Ctx {
@@ -560,7 +557,7 @@ void launch_stride(const T* own_src, const T* nbr_src, T* dst, const T* b, const
 }
 
 // LDS row strides the kernel is built for: a row of up to stride - 4 columns
-// (the nearest one costs at most a quarter more LDS from 32 columns on).  With
+// (the nearest one costs at most 37 % more LDS from 32 columns on, at 34).  With
 // the stride a constant every stencil read is a base register and an immediate
 // offset; with the row length a run-time value, as it was for all but five of
 // them, the address arithmetic cost more than the stencil: per FP32 sweep 581
@@ -573,7 +570,7 @@ void launch_stride(const T* own_src, const T* nbr_src, T* dst, const T* b, const
 template <typename T>
 constexpr bool has_stride(int stride) { return sizeof(T) == 4 || stride != 768 + 2 * kPad; }
 
-int row_stride(int nx, int bytes_per_value) {
+constexpr int row_stride(int nx, int bytes_per_value) {
   if (nx == 768 && bytes_per_value == 8) return kSplitStride;
 #define QS_FIT(N) \
   if (nx + 2 * kPad <= N) return N;
@@ -581,6 +578,13 @@ int row_stride(int nx, int bytes_per_value) {
 #undef QS_FIT
   return 0;
 }
+
+constexpr bool slack_within(int percent) {
+  for (int nx = 32; nx <= 512; nx += 2)
+    if (100 * row_stride(nx, 4) > (100 + percent) * (nx + 2 * kPad)) return false;
+  return true;
+}
+static_assert(slack_within(37) && !slack_within(36), "the strides' slack as stated");
 
 template <typename T, int S>
 void set_lds_limit_one(int bytes) {

@@ -19,8 +19,8 @@
 // Measured, us per sweep, row sweep before -> now: 32^3 36.5 -> 8.2 (FP64),
 // 29.3 -> 8.6 (FP32); 64 x 64 x 32 37.1 -> 10.7, 29.8 -> 8.0; 96^3 42.8 -> 34.0,
 // 32.1 -> 17.2; 128^3 67.2 -> 61.4, 38.3 -> 31.7.  At 32^3 that is about three
-// launches' worth: the fill (two rounds of loads) and eight phases of 33 LDS
-// reads per node.
+// launches' worth: the fill (two rounds of loads) and eight phases of 42 LDS
+// reads per node (18 along the axes, 24 mixed).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
