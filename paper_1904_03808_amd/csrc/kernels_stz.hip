@@ -6,6 +6,7 @@
 // are [3][nz+1][ny][nx].  One thread per cell or per interior node; these
 // kernels stream their inputs once and are HBM-bound.
 #include <algorithm>
+#include <type_traits>
 
 #include "device.h"
 
@@ -93,10 +94,11 @@ __device__ __forceinline__ double half_exp(double b) {
   return large ? (0.5 * e) * e : 0.5 * e;
 }
 
-// cosh(b) for any b; exp(-|b|) counts below 20.
+// cosh(b); exp(-|b|) counts below 20.  LARGE: for any b, otherwise |b| <= 709.
+template <bool LARGE>
 __device__ __forceinline__ double cosh_of(double b) {
   b = fabs(b);
-  const double e = half_exp(b);
+  const double e = LARGE ? half_exp(b) : 0.5 * exp(b);
   return b < 20.0 ? e + 0.5 * exp(-b) : e;
 }
 
@@ -146,10 +148,12 @@ __device__ __forceinline__ double eno_2h(double fm2, double fm1, double f0, doub
   return fp1 - fm1;
 }
 
-// D^pl alone (Eq. stz_dpl) from A = exp(-1/chi) exp(-delta/T) / tau0.
+// D^pl alone (Eq. stz_dpl) from A = exp(-1/chi) exp(-delta/T) / tau0 (LARGE: see
+// cosh_of).
+template <bool LARGE>
 __device__ __forceinline__ double plastic_D(double sbar, double A, const StzArgs& a) {
   if (!(sbar > a.s_y)) return 0.0;
-  return A * cosh_of(a.beta * sbar) * (1.0 - a.s_y / sbar);
+  return A * cosh_of<LARGE>(a.beta * sbar) * (1.0 - a.s_y / sbar);
 }
 
 constexpr int kMaxSubsteps = 65536;
@@ -303,18 +307,26 @@ __device__ __forceinline__ void stz_update(const double* __restrict__ sigma,
     const double A = exp(-1.0 / x) * a.rate0;
     if (sbar > a.s_y) {
       double lo = a.s_y, hi = sbar;
-      for (int it = 0; it < kImplicitBisections; ++it) {
-        const double mid = 0.5 * (lo + hi);
-        const double g = mid - sbar + 2.0 * a.mu * a.dt * plastic_D(mid, A, a);
-        if (g < 0.0)
-          lo = mid;
-        else
-          hi = mid;
-      }
+      auto bisect = [&](auto large) {
+        for (int it = 0; it < kImplicitBisections; ++it) {
+          const double mid = 0.5 * (lo + hi);
+          const double g = mid - sbar + 2.0 * a.mu * a.dt * plastic_D<decltype(large)::value>(mid, A, a);
+          if (g < 0.0)
+            lo = mid;
+          else
+            hi = mid;
+        }
+      };
+      // sbar is the largest argument: chosen once here, the care past 709 is not
+      // taken 64 times (96 x 96 x 24: 45.6 us inside the loop, 41 without)
+      if (fabs(a.beta * sbar) > 709.0)
+        bisect(std::true_type());
+      else
+        bisect(std::false_type());
       s1 = hi;
     }
     const double scale = sbar > a.s_y ? s1 / (sbar > 0.0 ? sbar : 1.0) : 1.0;
-    const double D1 = plastic_D(s1, A, a);
+    const double D1 = plastic_D<true>(s1, A, a);
     const double cg = (a.dt / a.c0) * (2.0 * s1 * D1 / a.s_y);
     xn = (x + cg * a.chi_inf) / (1.0 + cg);
 #pragma unroll
